@@ -261,37 +261,33 @@ __global__ __launch_bounds__(64) void k_frag_prep(const float* __restrict__ W, i
 
 // Encoder contraction in the epilogue of the FFN output projection (z = h W_down,
 // Sec. 3.2 places the encoder right after the feed-forward layer): the block's
-// rounded 256 x 256 tile of z goes to LDS (its four stage buffers, 64 rows
-// each), and wave w multiplies rows 32 w .. 32 w + 31 of it by the tile's 256
-// rows of W_e (float32, as hi + lo bf16 fragments prepared by k_frag_prep, in
-// X), writing the float32 partial sum D[tile column][row][0 .. r).  The
-// partials are added in tile order by k_enc_finish.
-template <int BM, int BN, int WM, int WN, int FM, int FN>
-__device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (&acc)[FM][FN], __bf16* q0,
-                                                __bf16* q1, __bf16* q2, __bf16* q3, int m0, int n0) {
-  static_assert(BM == 256 && BN == 256 && WM * WN == 8, "the encoder epilogue runs on 256 x 256 tiles of 8 waves");
+// rounded 256 x 256 tile of z goes to LDS (over the stage buffers), and wave w
+// multiplies rows 32 w .. 32 w + 31 of it by the tile's 256 rows of W_e
+// (float32, as hi + lo bf16 fragments prepared by k_frag_prep, in X), writing
+// the float32 partial sum D[tile column][row][0 .. r).  The partials are added
+// in tile order by k_enc_finish.
+__device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (&acc)[8][4], __bf16* tile, int m0,
+                                                int n0) {
+  constexpr int BN = 256;
   const int lane = threadIdx.x & 63, row16 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave % WM, wn = wave / WM;
-  auto quarter = [&](int q) { return q == 0 ? q0 : (q == 1 ? q1 : (q == 2 ? q2 : q3)); };
+  const int wm = wave >> 2, wn = wave & 3;
   __syncthreads();  // every wave has finished reading the last stage
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int ml = (wm * FM + i) * 16 + row16;
-    __bf16* q = quarter(ml >> 6);
+  for (int i = 0; i < 8; ++i) {
+    const int ml = (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + row16;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int nl = (wn * FN + j) * 16 + 4 * grp;
+    for (int j = 0; j < 4; ++j) {
+      const int nl = (j >> 1) * 128 + wn * 32 + (j & 1) * 16 + 4 * grp;
       bf16x4 h;
 #pragma unroll
       for (int e = 0; e < 4; ++e) h[e] = (__bf16)acc[i][j][e];
-      *reinterpret_cast<uint2*>(q + (ml & 63) * 256 + resbm::wide_col(ml & 63, nl)) = __builtin_bit_cast(uint2, h);
+      *reinterpret_cast<uint2*>(tile + ml * 256 + resbm::wide_col(ml, nl)) = __builtin_bit_cast(uint2, h);
     }
   }
   __syncthreads();
   const rsrc_t rw = make_rsrc(g.X, g.x_bytes);
   const int r = g.x_cols, nt = n0 / BN, nc = (r + 63) / 64 * 4;
-  const __bf16* zq = quarter(wave >> 1);
   const rsrc_t rd = make_rsrc(g.D, g.d_bytes);
   for (int jg = 0; jg < r; jg += 64) {
     f32x4 a2[2][4];
@@ -310,8 +306,8 @@ __device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (
       }
 #pragma unroll
       for (int ib = 0; ib < 2; ++ib) {
-        const int row = 32 * (wave & 1) + 16 * ib + row16, col = 32 * ks + 8 * grp;
-        zf[ib] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(zq + row * 256 + resbm::wide_col(row, col)));
+        const int row = 32 * wave + 16 * ib + row16, col = 32 * ks + 8 * grp;
+        zf[ib] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(tile + row * 256 + resbm::wide_col(row, col)));
       }
 #pragma unroll
       for (int jb = 0; jb < 4; ++jb)
@@ -336,19 +332,547 @@ __device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (
   }
 }
 
-// LATE (direct staging only): the next stage's loads are issued after the
-// first half of the current stage's products instead of before them, so the
-// products start right after the barrier; it pays where a block's K depth is
-// moderate (2-10 % at 1024 and 4096) and costs where it is long (3 % at 14336).
-template <bool AK, bool BKC, int BM, int BN, int WM, int WN, int EPI, bool PHI_A, bool LATE = false>
+// ---------------------------------------------------------------- the pipelined core
+// The operand tiles of the pipelined kernels are staged in "halves": 128
+// indices along M or N by 64 along K (16 KiB), moved straight into LDS by the
+// block's 8 waves (two 1 KiB buffer loads per wave and half, LDS destination).
+// A K-contiguous half is laid out [128][64] with kc_col's permutation, the
+// other [64][128] with tr_col's; each lane fetches the 16-byte chunk whose
+// position it fills (both permutations are XORs, their own inverse).
+constexpr int kHalf = 128 * KT;  // elements
+
+template <bool KC>
+struct HalfSrc {
+  uint32_t off[2];   // byte offset of this lane's chunk in the first half, per load
+  int k[2];          // its first k within the stage
+  uint32_t step;     // bytes from the first half to the second
+  __device__ __forceinline__ void init(int64_t ld, int wave, int lane) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int o = (p * 8 + wave) * 1024 + lane * 16;
+      if constexpr (KC) {
+        const int row = o >> 7, pc = (o >> 4) & 7;
+        k[p] = 8 * ((pc ^ (row >> 1)) & 7);  // kc_col's XOR
+        off[p] = (uint32_t)((row * ld + k[p]) * 2);
+      } else {
+        const int row = o >> 8, pc = (o >> 4) & 15;
+        const int f = ((row & 3) | ((row >> 1) & 4)) << 1;  // tr_col's XOR
+        k[p] = row;
+        off[p] = (uint32_t)((row * ld + 8 * (pc ^ f)) * 2);
+      }
+    }
+    step = (uint32_t)(KC ? 256 * ld : 256);
+  }
+  // Half h of the stage whose descriptor is src, krem the K that is left from
+  // the stage's start (chunks at or beyond it become zeros).  Indices past the
+  // operand's extent need no test: a K-contiguous row past the last lies outside
+  // the descriptor, and a column past the last holds some other element of the
+  // operand, which only reaches outputs that are not stored.
+  __device__ __forceinline__ void issue(rsrc_t src, int h, int krem, __bf16* half, int wave) const {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const uint32_t o = k[p] < krem ? off[p] + (h ? step : 0u) : kOOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          src, (__attribute__((address_space(3))) void*)(half + (p * 8 + wave) * 512), 16, o, 0, 0, 0);
+    }
+  }
+};
+
+// Byte offset of this lane's part of fragment (0, 0) in a staged half, for a
+// wave whose indices start at w0 (a multiple of 32): see read_frags.
+template <bool KC>
+__device__ __forceinline__ uint32_t frag_base(int w0, int row16, int grp) {
+  if constexpr (KC) {
+    return 2u * ((w0 + row16) * KT + ((grp ^ (row16 >> 1)) & 7) * 8);
+  } else {
+    const int f = (((row16 >> 2) & 3) | ((grp & 1) << 2)) << 1;
+    return 2u * ((8 * grp + (row16 >> 2)) * 128 + (((w0 >> 3) + ((row16 & 3) >> 1)) ^ f) * 8 + 4 * (row16 & 1));
+  }
+}
+
+// Fragments f[i][kk] (indices w0 + 16 i .. + 15, 32-deep K step kk) of the half
+// OFF bytes past the one that `a` (an LDS byte address, frag_base included)
+// points into, with the wait for them.  The reads are one asm block because
+// the compiler, seeing them beside the buffer loads that fill other halves,
+// waits for those loads too (vmcnt(6) where 12 may stay in flight).
+typedef long i64x2 __attribute__((ext_vector_type(2)));
+template <bool KC, int OFF>
+__device__ __forceinline__ void read_frags4(bf16x8 (&f)[4][2], uint32_t a) {
+  if constexpr (KC) {
+    const uint32_t b = a ^ 64;
+    asm volatile(
+        "ds_read_b128 %0, %8 offset:%10\n\tds_read_b128 %1, %9 offset:%10\n\t"
+        "ds_read_b128 %2, %8 offset:%11\n\tds_read_b128 %3, %9 offset:%11\n\t"
+        "ds_read_b128 %4, %8 offset:%12\n\tds_read_b128 %5, %9 offset:%12\n\t"
+        "ds_read_b128 %6, %8 offset:%13\n\tds_read_b128 %7, %9 offset:%13\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[1][0]), "=&v"(f[1][1]), "=&v"(f[2][0]), "=&v"(f[2][1]),
+          "=&v"(f[3][0]), "=&v"(f[3][1])
+        : "v"(a), "v"(b), "n"(OFF), "n"(OFF + 2048), "n"(OFF + 4096), "n"(OFF + 6144)
+        : "memory");
+  } else {
+    const uint32_t b = a ^ 32, c = a ^ 64, d = a ^ 96;
+    long h[4][4];
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16 offset:%20\n\tds_read_b64_tr_b16 %1, %16 offset:%21\n\t"
+        "ds_read_b64_tr_b16 %2, %16 offset:%22\n\tds_read_b64_tr_b16 %3, %16 offset:%23\n\t"
+        "ds_read_b64_tr_b16 %4, %17 offset:%20\n\tds_read_b64_tr_b16 %5, %17 offset:%21\n\t"
+        "ds_read_b64_tr_b16 %6, %17 offset:%22\n\tds_read_b64_tr_b16 %7, %17 offset:%23\n\t"
+        "ds_read_b64_tr_b16 %8, %18 offset:%20\n\tds_read_b64_tr_b16 %9, %18 offset:%21\n\t"
+        "ds_read_b64_tr_b16 %10, %18 offset:%22\n\tds_read_b64_tr_b16 %11, %18 offset:%23\n\t"
+        "ds_read_b64_tr_b16 %12, %19 offset:%20\n\tds_read_b64_tr_b16 %13, %19 offset:%21\n\t"
+        "ds_read_b64_tr_b16 %14, %19 offset:%22\n\tds_read_b64_tr_b16 %15, %19 offset:%23\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(h[0][0]), "=&v"(h[0][1]), "=&v"(h[0][2]), "=&v"(h[0][3]), "=&v"(h[1][0]), "=&v"(h[1][1]),
+          "=&v"(h[1][2]), "=&v"(h[1][3]), "=&v"(h[2][0]), "=&v"(h[2][1]), "=&v"(h[2][2]), "=&v"(h[2][3]),
+          "=&v"(h[3][0]), "=&v"(h[3][1]), "=&v"(h[3][2]), "=&v"(h[3][3])
+        : "v"(a), "v"(b), "v"(c), "v"(d), "n"(OFF), "n"(OFF + 1024), "n"(OFF + 8192), "n"(OFF + 9216)
+        : "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) f[i][kk] = __builtin_bit_cast(bf16x8, (i64x2){h[i][2 * kk], h[i][2 * kk + 1]});
+  }
+}
+template <bool KC, int OFF>
+__device__ __forceinline__ void read_frags2(bf16x8 (&f)[2][2], uint32_t a) {
+  if constexpr (KC) {
+    const uint32_t b = a ^ 64;
+    asm volatile(
+        "ds_read_b128 %0, %4 offset:%6\n\tds_read_b128 %1, %5 offset:%6\n\t"
+        "ds_read_b128 %2, %4 offset:%7\n\tds_read_b128 %3, %5 offset:%7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[1][0]), "=&v"(f[1][1])
+        : "v"(a), "v"(b), "n"(OFF), "n"(OFF + 2048)
+        : "memory");
+  } else {
+    const uint32_t b = a ^ 32;
+    long h[2][4];
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %8 offset:%11\n\t"
+        "ds_read_b64_tr_b16 %2, %8 offset:%12\n\tds_read_b64_tr_b16 %3, %8 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %4, %9 offset:%10\n\tds_read_b64_tr_b16 %5, %9 offset:%11\n\t"
+        "ds_read_b64_tr_b16 %6, %9 offset:%12\n\tds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(h[0][0]), "=&v"(h[0][1]), "=&v"(h[0][2]), "=&v"(h[0][3]), "=&v"(h[1][0]), "=&v"(h[1][1]),
+          "=&v"(h[1][2]), "=&v"(h[1][3])
+        : "v"(a), "v"(b), "n"(OFF), "n"(OFF + 1024), "n"(OFF + 8192), "n"(OFF + 9216)
+        : "memory");
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) f[i][kk] = __builtin_bit_cast(bf16x8, (i64x2){h[i][2 * kk], h[i][2 * kk + 1]});
+  }
+}
+
+// A block barrier that nothing is scheduled across.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Work items of a pipelined kernel: (K split, tile) pairs, tiles along N first.
+// XCD x (blocks x, x + 8, ...) is given a contiguous range of items, so that
+// the items in flight on one XCD share the rows of A through its L2, and its
+// blocks walk that range in turn.
+struct WorkList {
+  int next, end, stride;
+  __device__ __forceinline__ void init(int total) {
+    const int x = blockIdx.x & 7, li = blockIdx.x >> 3, G = gridDim.x;
+    const int begin = x * (total >> 3) + min(x, total & 7);
+    end = begin + (total >> 3) + (x < (total & 7) ? 1 : 0);
+    stride = (G >> 3) + (x < (G & 7) ? 1 : 0);
+    next = begin + li;
+  }
+};
+struct Item {
+  int m0, n0, split, kbeg, klen;
+};
+
+// Reads the operands of the items in order, one 64-deep stage after another,
+// running ahead of the products across item boundaries.
+template <bool AK, bool BKC, int BM, int BN>
+struct StageCursor {
+  HalfSrc<AK> ha;
+  HalfSrc<BKC> hb;
+  uint32_t oa, ob, sa, sb;  // byte offsets of the next stage, and per stage
+  int krem;                 // K left in the item (<= 0: stages of zeros)
+  __device__ __forceinline__ void start(const GemmArgs& g, const Item& it) {
+    oa = (uint32_t)((AK ? (int64_t)it.m0 * g.lda + it.kbeg : (int64_t)it.kbeg * g.lda + it.m0) * 2);
+    ob = (uint32_t)((BKC ? (int64_t)it.n0 * g.ldb + it.kbeg : (int64_t)it.kbeg * g.ldb + it.n0) * 2);
+    krem = it.klen;
+  }
+  __device__ __forceinline__ void init(const GemmArgs& g, int wave, int lane) {
+    ha.init(g.lda, wave, lane);
+    hb.init(g.ldb, wave, lane);
+    sa = (uint32_t)((AK ? KT : KT * g.lda) * 2);
+    sb = (uint32_t)((BKC ? KT : KT * g.ldb) * 2);
+  }
+  __device__ __forceinline__ rsrc_t desc(const void* p, int64_t bytes, uint32_t o) const {
+    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(p) + (krem > 0 ? o : 0u), (short)0,
+                                             krem > 0 ? (uint32_t)bytes - o : 0u, 0x00020000);
+  }
+  __device__ __forceinline__ rsrc_t a(const GemmArgs& g) const { return desc(g.A, g.a_bytes, oa); }
+  __device__ __forceinline__ rsrc_t b(const GemmArgs& g) const { return desc(g.B, g.b_bytes, ob); }
+  __device__ __forceinline__ void advance() {
+    oa += sa;
+    ob += sb;
+    krem -= KT;
+  }
+};
+
+// The i-th work item's tile and K range.
+template <int BM, int BN>
+__device__ __forceinline__ Item item_of(const GemmArgs& g, int i) {
+  const int tn = (g.N + BN - 1) / BN, tm = (g.M + BM - 1) / BM;
+  Item it;
+  it.split = i / (tm * tn);
+  const int t = i - it.split * (tm * tn);
+  it.m0 = t / tn * BM;
+  it.n0 = t % tn * BN;
+  it.kbeg = it.split * g.kc;
+  it.klen = min(g.K, it.kbeg + g.kc) - it.kbeg;
+  return it;
+}
+
+// Stores four consecutive columns n .. n + 3 of row m of the result with the
+// epilogue EPI (out of range: dropped).  Offsets of elements in range are below
+// 4 GiB, so 32-bit arithmetic is exact for them.
+template <int EPI>
+__device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m, int n,
+                                         f32x4 v) {
+  const bool ok = m < g.M && n < g.N;
+  if constexpr (EPI == kEpiF32 || EPI == kEpiPart) {
+    const uint32_t off = EPI == kEpiPart ? ((uint32_t)split * g.M + m) * g.N + n : (uint32_t)m * (uint32_t)g.ldc + n;
+    bst16(rc, ok ? off * 4 : kOOB, __builtin_bit_cast(uint4, v));
+  } else {
+    if constexpr (EPI == kEpiDphi || EPI == kEpiAdd) {
+      const bool xok = ok && (EPI == kEpiDphi || n < g.x_cols);
+      const uint2 xr = bld8(rx, xok ? ((uint32_t)m * (uint32_t)g.ldx + n) * 2 : kOOB);
+      const bf16x4 x = __builtin_bit_cast(bf16x4, xr);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (EPI == kEpiDphi) v[e] *= resbm::silu_grad((float)x[e]);
+        else v[e] += (float)x[e];
+      }
+    }
+    bf16x4 h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) h[e] = (__bf16)v[e];
+    bst8(rc, ok ? ((uint32_t)m * (uint32_t)g.ldc + n) * 2 : kOOB, __builtin_bit_cast(uint2, h));
+    if constexpr (EPI == kEpiBf16Phi) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (__bf16)silu(v[e]);  // from the float32 accumulator
+      bst8(rd, ok ? ((uint32_t)m * (uint32_t)g.ldd + n) * 2 : kOOB, __builtin_bit_cast(uint2, h));
+    }
+  }
+}
+
+// The value v, opaque to the optimizer: what an epilogue derives from it is
+// formed there, not hoisted out of the loop over work items (the addresses of
+// 32 stores would take the registers that the stages need).
+__device__ __forceinline__ int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// C = A B in 256 x 256 tiles, 8 waves; wave (wm, wn) owns rows 128 h + 64 wm ..
+// + 63 and columns 128 q + 32 wn .. + 31 for h, q = 0, 1.  A 64-deep stage is
+// four phases, one quadrant (h, q) of 16 products each.  A phase is a load
+// section (issue one half of the stage after next into the half that every
+// wave finished reading in the phase before, read the 8 or 4 fragments that the
+// quadrant lacks, wait for them and for the half that the next phase reads)
+// and a product section, each ended by a barrier; waves 4-7 run one section
+// behind waves 0-3, so each SIMD has one wave multiplying while the other
+// loads.  The stage before a half is read, 6 others are in flight behind it
+// (vmcnt(12)); nothing drains.  Stages of even and odd parity take B's halves
+// in opposite order, so that a stage's first B half is read in the last phase
+// of the stage before and the phases read 8, 4, 8, 4 fragments.
+// The stream of stages runs on across work items (K extents padded to an even
+// number of stages): the next tile's operands load while this one's results
+// are stored.  kEpiEncode reuses the stage buffers and runs one item per block.
+// What bounds it: matrix cores at the clock this load allows (a registers-only
+// probe of the same products reaches 2.0 PFLOP/s), then the operand stream.
+// 16384 x 4096 x 14336: 1.47 PFLOP/s, against 1.17 for the double-buffered
+// kernel it replaced (one barrier and a full drain per stage) and 1.31 for the
+// library; without the half-phase offset of the waves 1.28.
+template <bool AK, bool BKC, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
+  constexpr int BM = 256, BN = 256;
+  __shared__ __attribute__((aligned(1024))) __bf16 smem[8 * kHalf];  // [parity][A0 A1 B0 B1]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row16 = lane & 15, grp = lane >> 4;
+  const int wm = wave >> 2, wn = wave & 3;
+
+  WorkList wl;
+  wl.init(total);
+  Item cur = item_of<BM, BN>(g, wl.next);
+  StageCursor<AK, BKC, BM, BN> cs;
+  cs.init(g, wave, lane);
+  cs.start(g, cur);
+
+  f32x4 acc[8][4];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  bf16x8 fa[4][2], fb0[2][2], fb1[2][2];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const uint32_t la = lds0 + frag_base<AK>(wm * 64, row16, grp), lb = lds0 + frag_base<BKC>(wn * 32, row16, grp);
+  constexpr uint32_t ODD = 8 * kHalf;  // bytes from the even to the odd stage's halves
+  constexpr int A0 = 0, A1 = 2 * kHalf, B0 = 4 * kHalf, B1 = 6 * kHalf;
+  auto mul = [&](int h, int q, const bf16x8 (&fb)[2][2]) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[4 * h + i][2 * q + j] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][kk], fa[i][kk], acc[4 * h + i][2 * q + j], 0, 0, 0);
+  };
+  // end of a load section; `st`: the previous item's stores (at least 32 per
+  // lane) were issued after the half waited for
+  auto loaded = [&](bool st) {
+    if (st) asm volatile("s_waitcnt vmcnt(44)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    phase_barrier();
+  };
+  __bf16* const even = smem;
+  __bf16* const odd = smem + 4 * kHalf;
+
+  // two stages; the halves of the two stages after them are issued
+  auto pair = [&](bool st) {
+    {
+      const rsrc_t ra = cs.a(g), rb = cs.b(g);
+      cs.hb.issue(rb, 0, cs.krem, even + 2 * kHalf, wave);
+      read_frags4<AK, A0>(fa, la);
+      loaded(st);
+      mul(0, 0, fb0);
+      phase_barrier();
+      cs.ha.issue(ra, 0, cs.krem, even, wave);
+      read_frags2<BKC, B1>(fb1, lb);
+      loaded(st);
+      mul(0, 1, fb1);
+      phase_barrier();
+      cs.hb.issue(rb, 1, cs.krem, even + 3 * kHalf, wave);
+      read_frags4<AK, A1>(fa, la);
+      loaded(st);
+      mul(1, 1, fb1);
+      phase_barrier();
+      cs.ha.issue(ra, 1, cs.krem, even + kHalf, wave);
+      read_frags2<BKC, B1>(fb1, lb + ODD);
+      loaded(st);
+      mul(1, 0, fb0);
+      phase_barrier();
+      cs.advance();
+    }
+    {
+      const rsrc_t ra = cs.a(g), rb = cs.b(g);
+      cs.hb.issue(rb, 1, cs.krem, odd + 3 * kHalf, wave);
+      read_frags4<AK, A0>(fa, la + ODD);
+      loaded(st);
+      mul(0, 1, fb1);
+      phase_barrier();
+      cs.ha.issue(ra, 0, cs.krem, odd, wave);
+      read_frags2<BKC, B0>(fb0, lb + ODD);
+      loaded(st);
+      mul(0, 0, fb0);
+      phase_barrier();
+      cs.hb.issue(rb, 0, cs.krem, odd + 2 * kHalf, wave);
+      read_frags4<AK, A1>(fa, la + ODD);
+      loaded(false);
+      mul(1, 0, fb0);
+      phase_barrier();
+      cs.ha.issue(ra, 1, cs.krem, odd + kHalf, wave);
+      read_frags2<BKC, B0>(fb0, lb);
+      loaded(false);
+      mul(1, 1, fb1);
+      phase_barrier();
+      cs.advance();
+    }
+  };
+
+  // stages 0 and 1, in the order in which their halves are read
+  {
+    const rsrc_t ra = cs.a(g), rb = cs.b(g);
+    cs.hb.issue(rb, 0, cs.krem, even + 2 * kHalf, wave);
+    cs.ha.issue(ra, 0, cs.krem, even, wave);
+    cs.hb.issue(rb, 1, cs.krem, even + 3 * kHalf, wave);
+    cs.ha.issue(ra, 1, cs.krem, even + kHalf, wave);
+    cs.advance();
+  }
+  {
+    const rsrc_t ra = cs.a(g), rb = cs.b(g);
+    cs.hb.issue(rb, 1, cs.krem, odd + 3 * kHalf, wave);
+    cs.ha.issue(ra, 0, cs.krem, odd, wave);
+    cs.hb.issue(rb, 0, cs.krem, odd + 2 * kHalf, wave);
+    cs.ha.issue(ra, 1, cs.krem, odd + kHalf, wave);
+    cs.advance();
+  }
+  asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+  phase_barrier();
+  read_frags2<BKC, B0>(fb0, lb);
+  phase_barrier();
+  if (wm == 1) phase_barrier();  // waves 4-7 run one section behind
+
+  const rsrc_t rc = make_rsrc(g.C, g.c_bytes), rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
+  bool stored = false;
+  for (;;) {
+    const int npair = (cur.klen + 2 * KT - 1) / (2 * KT);
+    wl.next += wl.stride;
+    const bool more = wl.next < wl.end;
+    Item nxt = cur;
+    if (more) nxt = item_of<BM, BN>(g, wl.next);
+    // before the last pair the cursor goes on to the next item (or to stages of zeros)
+    auto go_on = [&]() {
+      if (more) cs.start(g, nxt);
+      else cs.krem = 0;
+    };
+    for (int p = 0; p < npair; ++p) {
+      if (p == npair - 1) go_on();
+      pair(stored && p == 0);
+    }
+    if constexpr (EPI != kEpiEncode) {
+      const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          store_c4<EPI>(g, rc, rx, rd, cur.split, mr + (i >> 2) * 128 + (i & 3) * 16, nr + (j >> 1) * 128 + (j & 1) * 16,
+                        acc[i][j]);
+    }
+    if (EPI == kEpiEncode || !more) break;
+    stored = true;
+    cur = nxt;
+    clear();
+  }
+  if (wm == 0) phase_barrier();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (EPI == kEpiEncode) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        store_c4<kEpiBf16>(g, rc, rx, rd, 0, cur.m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + row16,
+                           cur.n0 + (j >> 1) * 128 + wn * 32 + (j & 1) * 16 + 4 * grp, acc[i][j]);
+    encode_epilogue(g, acc, smem, cur.m0, cur.n0);
+  }
+}
+
+// C = A B in 128 x 128 tiles, for results with too few 256 x 256 tiles to fill
+// the chip: 8 waves of 64 x 32, one phase of 16 products per 64-deep stage, the
+// stages in a ring of four (128 KiB), three in flight; sections, wave offset
+// and the stream across items as in k_gemm_big.
+template <bool AK, bool BKC, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_mid(GemmArgs g, int total) {
+  constexpr int BM = 128, BN = 128;
+  __shared__ __attribute__((aligned(1024))) __bf16 smem[8 * kHalf];  // [ring][A B]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row16 = lane & 15, grp = lane >> 4;
+  const int wm = wave >> 2, wn = wave & 3;
+
+  WorkList wl;
+  wl.init(total);
+  Item cur = item_of<BM, BN>(g, wl.next);
+  StageCursor<AK, BKC, BM, BN> cs;
+  cs.init(g, wave, lane);
+  cs.start(g, cur);
+  // the item that the cursor is on: stages left to issue, and the item after it
+  int left = (cur.klen + KT - 1) / KT;
+  int ahead = wl.next;
+
+  f32x4 acc[4][2];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  bf16x8 fa[4][2], fb[2][2];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  const uint32_t la = lds0 + frag_base<AK>(wm * 64, row16, grp), lb = lds0 + frag_base<BKC>(wn * 32, row16, grp);
+  auto issue = [&](int slot) {
+    __bf16* const p = smem + slot * 2 * kHalf;
+    const rsrc_t ra = cs.a(g), rb = cs.b(g);
+    cs.ha.issue(ra, 0, cs.krem, p, wave);
+    cs.hb.issue(rb, 0, cs.krem, p + kHalf, wave);
+    cs.advance();
+    if (--left == 0) {  // on to the next item, or to stages of zeros
+      ahead += wl.stride;
+      if (ahead < wl.end) {
+        const Item it = item_of<BM, BN>(g, ahead);
+        cs.start(g, it);
+        left = (it.klen + KT - 1) / KT;
+      } else {
+        cs.krem = 0;
+        left = 1;  // stays dead: krem only falls, `ahead` stays past the end
+      }
+    }
+  };
+  issue(0);
+  issue(1);
+  issue(2);
+  asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  phase_barrier();
+  if (wm == 1) phase_barrier();  // waves 4-7 run one section behind
+
+  const rsrc_t rc = make_rsrc(g.C, g.c_bytes), rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
+  int slot = 0;
+  bool stored = false;
+  for (;;) {
+    const int nst = (cur.klen + KT - 1) / KT;
+    for (int s = 0; s < nst; ++s) {
+      issue((slot + 3) & 3);
+      const uint32_t o = slot * 4 * kHalf;
+      read_frags4<AK, 0>(fa, la + o);
+      read_frags2<BKC, 2 * kHalf>(fb, lb + o);
+      // the next stage has landed; 8 stores follow it after an item's end
+      if (stored && s < 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      phase_barrier();
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][kk], fa[i][kk], acc[i][j], 0, 0, 0);
+      phase_barrier();
+      slot = (slot + 1) & 3;
+    }
+    const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) store_c4<EPI>(g, rc, rx, rd, cur.split, mr + 16 * i, nr + 16 * j, acc[i][j]);
+    wl.next += wl.stride;
+    if (wl.next >= wl.end) break;
+    stored = true;
+    cur = item_of<BM, BN>(g, wl.next);
+    clear();
+  }
+  if (wm == 0) phase_barrier();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// C = A B for the r-wide results (64 x {32, 64, 128} tiles), staged through
+// registers, double buffered, one barrier per 64-deep stage; PHI_A applies SiLU
+// to A's elements as they are staged.
+template <bool AK, bool BKC, int BM, int BN, int WM, int WN, int EPI, bool PHI_A>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs g) {
   constexpr int NTH = 64 * WM * WN;
   constexpr int FM = BM / (16 * WM), FN = BN / (16 * WN);
   static_assert(FM * 16 * WM == BM && FN * 16 * WN == BN, "wave tiling must cover the block tile");
-  // Direct-to-LDS staging for the 256 x 256 tiles without an A prologue; the
-  // others stage through registers.  Four separate LDS arrays keep the stage
-  // buffers distinct objects for the compiler's wait-count analysis.
-  constexpr bool kDma = BM == 256 && BN == 256 && !PHI_A;
   __shared__ __attribute__((aligned(16))) __bf16 s_a0[BM * KT], s_a1[BM * KT];
   __shared__ __attribute__((aligned(16))) __bf16 s_b0[BN * KT], s_b1[BN * KT];
 
@@ -389,96 +913,39 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs g) {
     products_kk(ta, tb, 1);
   };
 
-  if constexpr (kDma) {
-    constexpr int NW = WM * WN;
-    auto stage = [&](int s, __bf16* a, __bf16* b) {
-      dma_tile<AK, BM, NW>(ra, g.lda, m0, g.M, kbeg + s * KT, kend, a, wave, lane);
-      dma_tile<BKC, BN, NW>(rb, g.ldb, n0, g.N, kbeg + s * KT, kend, b, wave, lane);
-    };
-    // Stage s + 1 streams into the other buffers while stage s is multiplied;
-    // a stage is complete once every wave has seen its own loads land.
-    auto step = [&](int s, const __bf16* a, const __bf16* b, __bf16* na, __bf16* nb) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      if constexpr (LATE) {
-        products_kk(a, b, 0);
-        if (s + 1 < nst) stage(s + 1, na, nb);
-        products_kk(a, b, 1);
-      } else {
-        if (s + 1 < nst) stage(s + 1, na, nb);
-        products(a, b);
-      }
-    };
-    if (nst > 0) stage(0, s_a0, s_b0);
-    for (int s = 0; s < nst; s += 2) {
-      step(s, s_a0, s_b0, s_a1, s_b1);
-      if (s + 1 < nst) step(s + 1, s_a1, s_b1, s_a0, s_b0);
+  Operand<AK, BM, NTH> opa;
+  Operand<BKC, BN, NTH> opb;
+  if (nst > 0) {
+    opa.load(ra, g.lda, m0, g.M, kbeg, kend, tid);
+    opb.load(rb, g.ldb, n0, g.N, kbeg, kend, tid);
+    opa.template put<PHI_A>(s_a0, tid);
+    opb.template put<false>(s_b0, tid);
+  }
+  __syncthreads();
+  for (int s = 0; s < nst; ++s) {
+    const bool more = s + 1 < nst;
+    if (more) {
+      opa.load(ra, g.lda, m0, g.M, kbeg + (s + 1) * KT, kend, tid);
+      opb.load(rb, g.ldb, n0, g.N, kbeg + (s + 1) * KT, kend, tid);
     }
-  } else {
-    Operand<AK, BM, NTH> opa;
-    Operand<BKC, BN, NTH> opb;
-    if (nst > 0) {
-      opa.load(ra, g.lda, m0, g.M, kbeg, kend, tid);
-      opb.load(rb, g.ldb, n0, g.N, kbeg, kend, tid);
-      opa.template put<PHI_A>(s_a0, tid);
-      opb.template put<false>(s_b0, tid);
+    products(s & 1 ? s_a1 : s_a0, s & 1 ? s_b1 : s_b0);
+    if (more) {
+      opa.template put<PHI_A>(s & 1 ? s_a0 : s_a1, tid);
+      opb.template put<false>(s & 1 ? s_b0 : s_b1, tid);
     }
     __syncthreads();
-    for (int s = 0; s < nst; ++s) {
-      const bool more = s + 1 < nst;
-      if (more) {
-        opa.load(ra, g.lda, m0, g.M, kbeg + (s + 1) * KT, kend, tid);
-        opb.load(rb, g.ldb, n0, g.N, kbeg + (s + 1) * KT, kend, tid);
-      }
-      products(s & 1 ? s_a1 : s_a0, s & 1 ? s_b1 : s_b0);
-      if (more) {
-        opa.template put<PHI_A>(s & 1 ? s_a0 : s_a1, tid);
-        opb.template put<false>(s & 1 ? s_b0 : s_b1, tid);
-      }
-      __syncthreads();
-    }
   }
 
-  // Epilogue: lane (row16, grp) of tile (i, j) holds C[m][n .. n + 3].
+  // lane (row16, grp) of tile (i, j) holds C[m][n .. n + 3]
   const rsrc_t rc = make_rsrc(g.C, g.c_bytes);
   const rsrc_t rx = make_rsrc(g.X, g.x_bytes);
   const rsrc_t rd = make_rsrc(g.D, g.d_bytes);
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int m = m0 + (wm * FM + i) * 16 + row16;
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = n0 + (wn * FN + j) * 16 + 4 * grp;
-      const bool ok = m < g.M && n < g.N;
-      f32x4 v = acc[i][j];
-      if constexpr (EPI == kEpiF32 || EPI == kEpiPart) {
-        const int64_t off = EPI == kEpiPart ? (((int64_t)blockIdx.z * g.M + m) * g.N + n) * 4
-                                            : ((int64_t)m * g.ldc + n) * 4;
-        bst16(rc, ok ? (uint32_t)off : kOOB, __builtin_bit_cast(uint4, v));
-      } else {
-        if constexpr (EPI == kEpiDphi || EPI == kEpiAdd) {
-          const bool xok = ok && (EPI == kEpiDphi || n < g.x_cols);
-          const uint2 xr = bld8(rx, xok ? (uint32_t)(((int64_t)m * g.ldx + n) * 2) : kOOB);
-          const bf16x4 x = __builtin_bit_cast(bf16x4, xr);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if constexpr (EPI == kEpiDphi) v[e] *= resbm::silu_grad((float)x[e]);
-            else v[e] += (float)x[e];
-          }
-        }
-        bf16x4 h;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = (__bf16)v[e];
-        bst8(rc, ok ? (uint32_t)(((int64_t)m * g.ldc + n) * 2) : kOOB, __builtin_bit_cast(uint2, h));
-        if constexpr (EPI == kEpiBf16Phi) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) h[e] = (__bf16)silu(v[e]);  // from the float32 accumulator
-          bst8(rd, ok ? (uint32_t)(((int64_t)m * g.ldd + n) * 2) : kOOB, __builtin_bit_cast(uint2, h));
-        }
-      }
-    }
-  }
-  if constexpr (EPI == kEpiEncode) encode_epilogue<BM, BN, WM, WN, FM, FN>(g, acc, s_a0, s_a1, s_b0, s_b1, m0, n0);
+    for (int j = 0; j < FN; ++j)
+      store_c4<EPI>(g, rc, rx, rd, blockIdx.z, m0 + (wm * FM + i) * 16 + row16, n0 + (wn * FN + j) * 16 + 4 * grp,
+                    acc[i][j]);
 }
 
 // ---------------------------------------------------------------- decoder into RMSNorm + QKV
@@ -720,7 +1187,7 @@ using namespace resbm2;
 namespace {
 
 constexpr size_t kWsAlign2 = 256;
-constexpr int kTargetBlocks = 256;   // split-K aims at one block per compute unit
+constexpr int kNumBlocks = 256;      // compute units: persistent grids, and what split-K aims at
 
 using resbm_host::aligned;
 using resbm_host::extent;
@@ -733,13 +1200,25 @@ bool shape_ok2(int64_t T, int n, int m, int r) {
 }
 bool fits(size_t bytes) { return bytes <= (size_t)kMaxRange; }
 
-// Block tile shapes: 256 x 256 (8 waves of 128 x 64) for the n x m products,
-// 128 x 128 (4 waves of 64 x 64) where M or N is below 256, and a narrow one
-// for an r-wide output (N = r).  Products with M = r use 128 x 128; the rows
-// beyond r read nothing.
+// Block tile shapes: 256 x 256 and 128 x 128 for the n x m products (the
+// pipelined kernels), and a narrow one for an r-wide output (N = r).  Products
+// with M = r use 128 x 128; the rows beyond r only reach discarded outputs.
 enum Shape { kBig = 0, kWide = 1, kNarrow32 = 2, kNarrow64 = 3, kNarrow128 = 4 };
 
+// Weight gradients: 256 x 256 unless M or N is below it (their token splits
+// fill the chip either way).
 Shape wide_for(int M, int N) { return M >= 256 && N >= 256 ? kBig : kWide; }
+// T-row products (no split): a 64-deep stage of a full round of 256 blocks takes
+// 1.4 us in 256 x 256 tiles and 0.7 in 128 x 128 ones (a quarter of the work,
+// twice the operand bytes per product), so the small tiles win where they need
+// fewer than twice the rounds, i.e. where at most 64 large tiles would leave
+// most of the chip idle (1024 x 4096 x 14336: 161 against 258 us; 4096 x 4096 x
+// 14336, 256 large tiles: 582 against 343), and where half a large tile would be padding.
+Shape rows_for(int M, int N) {
+  const int64_t big = ((int64_t)(M + 255) / 256) * ((N + 255) / 256), mid = ((int64_t)(M + 127) / 128) * ((N + 127) / 128);
+  const int64_t rb = (big + 255) / 256, rm = (mid + 255) / 256;
+  return M <= 128 || N <= 128 || rm < 2 * rb ? kWide : kBig;
+}
 Shape narrow_for(int N) { return N <= 32 ? kNarrow32 : (N <= 64 ? kNarrow64 : kNarrow128); }
 int shape_bm(Shape s) { return s == kBig ? 256 : (s == kWide ? 128 : 64); }
 int shape_bn(Shape s) {
@@ -754,7 +1233,7 @@ struct Split {
 // split at least 4 stages deep.
 Split split_for(int M, int N, int K, Shape s) {
   const int64_t tiles = (int64_t)((M + shape_bm(s) - 1) / shape_bm(s)) * ((N + shape_bn(s) - 1) / shape_bn(s));
-  int64_t S = (kTargetBlocks + tiles - 1) / tiles;
+  int64_t S = (kNumBlocks + tiles - 1) / tiles;
   const int64_t maxS = std::max<int64_t>(1, K / (4 * KT));
   S = std::min(S, maxS);
   const int64_t per = (K + S - 1) / S;
@@ -784,25 +1263,37 @@ Plan2 make_plan2(int64_t T, int n, int m, int r) {
   return p;
 }
 
-template <bool AK, bool BKC, int BM, int BN, int WM, int WN, int EPI, bool PHI, bool LATE = false>
+template <bool AK, bool BKC, int BM, int BN, int WM, int WN, int EPI, bool PHI>
 void launch(const GemmArgs& g, int S, hipStream_t st) {
   const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  hipLaunchKernelGGL((k_gemm<AK, BKC, BM, BN, WM, WN, EPI, PHI, LATE>), dim3(tiles, 1, S), dim3(64 * WM * WN), 0, st,
-                     g);
+  hipLaunchKernelGGL((k_gemm<AK, BKC, BM, BN, WM, WN, EPI, PHI>), dim3(tiles, 1, S), dim3(64 * WM * WN), 0, st, g);
+}
+
+// One block per compute unit walks the S * tiles work items of a pipelined
+// kernel (kEpiEncode, which has the stage buffers to itself: a block per item).
+template <bool AK, bool BKC, int EPI>
+void launch_big(const GemmArgs& g, int S, hipStream_t st) {
+  const int total = S * ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  const int grid = EPI == kEpiEncode ? total : std::min(total, kNumBlocks);
+  hipLaunchKernelGGL((k_gemm_big<AK, BKC, EPI>), dim3(grid), dim3(512), 0, st, g, total);
+}
+template <bool AK, bool BKC, int EPI>
+void launch_mid(const GemmArgs& g, int S, hipStream_t st) {
+  const int total = S * ((g.M + 127) / 128) * ((g.N + 127) / 128);
+  hipLaunchKernelGGL((k_gemm_mid<AK, BKC, EPI>), dim3(std::min(total, kNumBlocks)), dim3(512), 0, st, g, total);
 }
 
 // Runs C = op(A) op(B) with the epilogue EPI and tile shape s.
 template <bool AK, bool BKC, int EPI, bool PHI>
 void gemm(Shape s, const GemmArgs& g, int S, hipStream_t st) {
+  if constexpr (!PHI) {
+    if (s == kBig) return launch_big<AK, BKC, EPI>(g, S, st);
+    if (s == kWide) return launch_mid<AK, BKC, EPI>(g, S, st);
+  }
   switch (s) {
-    case kBig:
-      if (std::min(g.K, g.kc) <= 4096) launch<AK, BKC, 256, 256, 2, 4, EPI, PHI, true>(g, S, st);
-      else launch<AK, BKC, 256, 256, 2, 4, EPI, PHI, false>(g, S, st);
-      break;
-    case kWide: launch<AK, BKC, 128, 128, 2, 2, EPI, PHI>(g, S, st); break;
     case kNarrow32: launch<AK, BKC, 64, 32, 4, 1, EPI, PHI>(g, S, st); break;
     case kNarrow64: launch<AK, BKC, 64, 64, 4, 1, EPI, PHI>(g, S, st); break;
-    case kNarrow128: launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st); break;
+    default: launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st); break;
   }
 }
 
@@ -884,9 +1375,9 @@ int32_t resbm2_encode_fwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, n, z, ld_z, bz, W1, m, bw1, u, m, bu);
   if (silu) {
     g.D = ws; g.ldd = m; g.d_bytes = (int64_t)bu;
-    gemm<true, false, kEpiBf16Phi, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m), g, 1, st);
   } else {
-    gemm<true, false, kEpiBf16, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
   }
   // b = x_attn[:, :r] + phi(u) W2
   g = args(Ti, r, m, silu ? ws : u, m, bu, W2, r, bw2, b, r, bb);
@@ -924,13 +1415,13 @@ int32_t resbm2_decode_fwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, r, b, r, bb, W3, m, bw3, v, m, bv);
   if (silu) {
     g.D = ws; g.ldd = m; g.d_bytes = (int64_t)bv;
-    gemm<true, false, kEpiBf16Phi, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m), g, 1, st);
   } else {
-    gemm<true, false, kEpiBf16, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
   }
   // z~ = phi(v) W4
   g = args(Ti, n, m, silu ? ws : v, m, bv, W4, n, bw4, z_tilde, ld_zt, bzt);
-  gemm<true, false, kEpiBf16, false>(wide_for(Ti, n), g, 1, st);
+  gemm<true, false, kEpiBf16, false>(rows_for(Ti, n), g, 1, st);
   return resbm_host::launch_status();
 }
 
@@ -974,9 +1465,9 @@ int32_t resbm2_decode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, n, g_zt, ld_gzt, bg, W4, n, bw4, g_v, m, bv);
   if (silu) {
     g.X = v; g.ldx = m; g.x_bytes = (int64_t)bv;
-    gemm<true, true, kEpiDphi, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiDphi, false>(rows_for(Ti, m), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
   }
   // dW4 = phi(v)^T g_zt   (A(i, k) = phi(v)[k][i], B(k, j) = g_zt[k][j]); phi(v) formed once
   if (silu) {
@@ -1042,9 +1533,9 @@ int32_t resbm2_encode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, r, g_b, r, bgb, W2, r, bw2, g_u, m, bu);
   if (silu) {
     g.X = u; g.ldx = m; g.x_bytes = (int64_t)bu;
-    gemm<true, true, kEpiDphi, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiDphi, false>(rows_for(Ti, m), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(wide_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
   }
   // dW2 = phi(u)^T g_b
   g = args(m, r, Ti, u, m, bu, g_b, r, bgb, nullptr, 0, 0);
@@ -1057,9 +1548,9 @@ int32_t resbm2_encode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   g = args(Ti, n, m, g_u, m, bu, W1, m, bw1, g_z, ld_gz, bgz);
   if (fused) {
     g.X = g_b; g.ldx = r; g.x_bytes = (int64_t)bgb; g.x_cols = r;
-    gemm<true, true, kEpiAdd, false>(wide_for(Ti, n), g, 1, st);
+    gemm<true, true, kEpiAdd, false>(rows_for(Ti, n), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(wide_for(Ti, n), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, n), g, 1, st);
     if (g_x) {
       const int64_t cnt = T * (r / 4);
       hipLaunchKernelGGL(k_skip_grad, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, T, r,
@@ -1121,7 +1612,7 @@ int32_t resbm_ffn_encode_fwd(int64_t T, int32_t d_ff, int32_t n, int32_t r, int3
   GemmArgs g = args((int)T, n, d_ff, h, ld_h, bh, W_down, n, bwd, z, ld_z, bz);
   g.X = wf; g.x_cols = r; g.x_bytes = (int64_t)(nf * 2048);
   g.D = ws; g.d_bytes = (int64_t)pb;
-  launch<true, false, 256, 256, 2, 4, kEpiEncode, false>(g, 1, st);
+  launch_big<true, false, kEpiEncode>(g, 1, st);
   const int64_t cnt = T * (r / 4);
   hipLaunchKernelGGL(k_enc_finish, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, T, r, (n + 255) / 256, act,
                      (const float*)ws, (const __bf16*)x_attn, ld_x, (__bf16*)b, a_save);
