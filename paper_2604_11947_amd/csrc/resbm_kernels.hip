@@ -2248,6 +2248,8 @@ __global__ __launch_bounds__(256) void k_expand_wide(int64_t T, int n, int r, co
 
 }  // namespace resbm
 
+#include "resbm_short.hpp"
+
 // ============================================================ host side
 using namespace resbm;
 
@@ -2295,6 +2297,19 @@ void launch_enc_fwd(const Plan& p, int act, const io_t* x, int64_t ld_x, const i
                        z, ld_z, wf, W_e, b, a_save);
   }
 }
+
+#if !RESBM_IO_F32_BUILD
+template <int JT, int MT>
+void launch_enc_fwd_short(const Plan& p, int act, const io_t* x, int64_t ld_x, const io_t* z, int64_t ld_z,
+                          const float* W_e, io_t* b, float* a_save, float* part, hipStream_t st) {
+  const dim3 grid((unsigned)ceil_div(p.T, 16 * MT), p.ef_nsl, (unsigned)ceil_div(p.NT, JT));
+  hipLaunchKernelGGL((k_enc_fwd_short<JT, MT>), grid, dim3(512), 0, st, p.T, p.n, p.r, p.RP, act, x, ld_x, z, ld_z, W_e,
+                     b, a_save, part);
+  if (p.ef_nsl > 1)
+    hipLaunchKernelGGL(k_enc_fwd_fin, dim3((unsigned)ceil_div(p.T * (p.r / 4), 64)), dim3(64), 0, st, p.T, p.r, p.RP,
+                       act, p.ef_nsl, (const float*)part, x, ld_x, b, a_save);
+}
+#endif
 
 // The expand kernel's input rows are fetched 8 elements per 16-byte load when
 // r % 8 == 0 (else as two 8-byte halves, one of them past r at r % 8 == 4);
@@ -2509,6 +2524,29 @@ int32_t encode_bwd_impl(int64_t T, int32_t n, int32_t r, int32_t act, const void
   const int64_t nb_dw = ceil_div((int64_t)n * (r / 4), 64);
   const int64_t nb_gx = (g_x && !fused) ? ceil_div(T * (r / 4), 256) : 0;
   const FinArgs fin{p.RP, dwp, p.eb_ntg, dW_e, accumulate, nb_dw, nb_dw + nb_gx, GB, (io_t*)g_x, ld_gx};
+#if !RESBM_IO_F32_BUILD
+  if (p.eb_once && window_ok(kOnceTS, ld_gz)) {
+    const int ntg = (int)ceil_div(T, (int64_t)kOnceTS * p.eb_once);
+#define CALL_EB(JT)                                                                                            \
+  do {                                                                                                         \
+    if (fused)                                                                                                 \
+      hipLaunchKernelGGL((k_enc_bwd_once<JT, true>), dim3(ntg, p.once_ncg), dim3(512), 0, s, T, n, r, p.RP,    \
+                         (int)(act == RESBM_ACT_SILU), Z, ld_z, W_e, AS, GB, GZ, ld_gz, dwp, p.eb_once);       \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_enc_bwd_once<JT, false>), dim3(ntg, p.once_ncg), dim3(512), 0, s, T, n, r, p.RP,   \
+                         (int)(act == RESBM_ACT_SILU), Z, ld_z, W_e, AS, GB, GZ, ld_gz, dwp, p.eb_once);       \
+  } while (0)
+    switch (short_jt(p.NT)) {
+      case 1: CALL_EB(1); break;
+      case 2: CALL_EB(2); break;
+      default: CALL_EB(4); break;
+    }
+#undef CALL_EB
+    hipLaunchKernelGGL(k_enc_bwd_fin, dim3((unsigned)fin.nb_all), dim3(256), 0, s, T, n, r, p.RP, (const float*)dwp,
+                       ntg, dW_e, accumulate, nb_dw, GB, (io_t*)g_x, ld_gx);
+    return launch_status();
+  }
+#endif
 #define CALL(NTV) launch_enc_bwd<NTV>(p, act, Z, ld_z, W_e, AS, GB, GZ, ld_gz, fused, dwp, gh_hi, gh_lo, fin, s)
   RESBM_DISPATCH_NT(p.NT, CALL)
 #undef CALL
@@ -2544,6 +2582,28 @@ int32_t resbm_encode_fwd(int64_t T, int32_t n, int32_t r, int32_t act, const voi
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
   void* wf = w + p.ef_wf_off;
+#if !RESBM_IO_F32_BUILD
+  if (p.ef_smt) {
+    const io_t* X = (const io_t*)x_attn;
+    const io_t* Z = (const io_t*)z;
+#define CALL_EF(JT)                                                                                           \
+  do {                                                                                                       \
+    if (p.ef_smt == 1)                                                                                       \
+      launch_enc_fwd_short<JT, 1>(p, act, X, ld_x, Z, ld_z, W_e, (io_t*)b, a_save, (float*)wf, s);           \
+    else if (p.ef_smt == 2)                                                                                  \
+      launch_enc_fwd_short<JT, 2>(p, act, X, ld_x, Z, ld_z, W_e, (io_t*)b, a_save, (float*)wf, s);           \
+    else                                                                                                     \
+      launch_enc_fwd_short<JT, 4>(p, act, X, ld_x, Z, ld_z, W_e, (io_t*)b, a_save, (float*)wf, s);           \
+  } while (0)
+    switch (short_jt(p.NT)) {
+      case 1: CALL_EF(1); break;
+      case 2: CALL_EF(2); break;
+      default: CALL_EF(4); break;
+    }
+#undef CALL_EF
+    return launch_status();
+  }
+#endif
   if (!ef_we_lds(p.NT)) {  // fragments for the kernels that read them prepared
     const int64_t nprep = (int64_t)(n / 32) * p.NT * 64;
     hipLaunchKernelGGL(k_enc_fwd_prep, dim3((unsigned)ceil_div(nprep, 64)), dim3(64), 0, s, W_e, n, r, p.NT, wf);
@@ -2614,6 +2674,29 @@ int32_t resbm_decode_bwd(int64_t T, int32_t n, int32_t r, const void* b, const f
   float* dwp = (float*)(w + p.db_dwp_off);
   const io_t* B = (const io_t*)b;
   const io_t* G = (const io_t*)g_zt;
+#if !RESBM_IO_F32_BUILD
+  if (p.db_once && window_ok(kOnceTS, ld_gzt)) {
+    const int ncg = p.once_ncg, ntg = (int)ceil_div(T, (int64_t)kOnceTS * p.db_once);
+    dwp = (float*)(w + p.db_once_dwp);
+    gbp = (float*)w;
+    const dim3 grid(ntg, ncg, (unsigned)ceil_div(p.NT, short_jt(p.NT)));
+#define CALL_DB(JT)                                                                                        \
+  hipLaunchKernelGGL((k_dec_bwd_once<JT>), grid, dim3(512), 0, s, T, n, r, p.RP, B, W_d, G, ld_gzt, gbp, \
+                     dwp, p.db_once)
+    switch (short_jt(p.NT)) {
+      case 1: CALL_DB(1); break;
+      case 2: CALL_DB(2); break;
+      default: CALL_DB(4); break;
+    }
+#undef CALL_DB
+    const int64_t nb_gb = ceil_div(T * (r / 4), 256);
+    const int64_t nb_dw = ceil_div((int64_t)r * (n / 4), 64);
+    hipLaunchKernelGGL(k_dec_bwd_fin, dim3((unsigned)(nb_gb + nb_dw)), dim3(256), 0, s, T, n, r, p.RP,
+                       (const float*)gbp, ncg, (const io_t*)g_id, ld_gid, (io_t*)g_b, (const float*)dwp, ntg, dW_d,
+                       accumulate, nb_gb);
+    return launch_status();
+  }
+#endif
   if (p.wide) {
     void* wf = w + p.db_wf_off;
     const int64_t nprep = (int64_t)(n / 32) * p.NT * 64;

@@ -163,6 +163,22 @@ constexpr int rw_ntw(int NT) {
   return ((NT + rw_rh(NT) - 1) / rw_rh(NT) + rw_waves(NT) - 1) / rw_waves(NT);
 }
 
+// ---- short streams (bf16 build; resbm_short.hpp).  Times: whole op, graph
+// replays, streaming kernels -> one-pass kernels.
+// encode_fwd: a block takes 16 MT tokens and splits its own rows of W_e.  One
+// wave of blocks over the chip, MT as small as that allows:
+//   T = 8, n = 4096, r = 32: 19.6 -> 6.5 us; T = 1024: 20.6 -> 9.0; T = 4096: 22.7 -> 17.0;
+//   T = 8192 (MT = 2): 25.3 -> 19.1, where T = 16384 would lose (29.8 against 37.1, MT = 4).
+// MT = 4 doubles what a block's split of W_e is spread over, and pays while
+// that split is small, n x 16 JT <= 65536 values:
+//   T = 16384, n = 2048, r = 16: 16.1 -> 14.2 us; T = 32768, n = 1024, r = 4: 18.8 -> 14.2.
+constexpr int kEfShortMt4 = 65536;
+// decode_bwd and encode_bwd: 64 x 256 tiles, streams of at most 2^25 elements:
+//   decode_bwd, r = 32, n = 4096: T = 1024 25.9 -> 16.6 us, T = 8192 33.5 -> 25.8, T = 16384 44.0 and 46.6;
+//   encode_bwd, r = 32, n = 4096: T = 1024 19.8 -> 15.4 us, T = 8192 35.7 -> 31.8, T = 16384 56.4 and 60.2.
+constexpr int64_t kOnceElems = (int64_t)1 << 25;
+constexpr int short_jt(int NT) { return NT <= 2 ? NT : 4; }  // j-tiles per block
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 inline size_t align_ws(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; }
@@ -189,6 +205,12 @@ struct Plan {
   int rw_nblk;                  // row contraction: blocks (see rw_tok, rw_rh)
   int tw_ncb, tw_ntg, tw_TB;    // token contraction: 128-column blocks x token groups of tw_TB tokens
   size_t db_wf_off;             // decode_bwd (wide): W_d fragments
+
+  // short streams
+  int ef_smt, ef_nsl;           // encode_fwd: 16 ef_smt tokens per block (0: not taken), ef_nsl slices of n
+  int db_once, eb_once;         // 64-token steps per block of the backward ops, 0: not taken
+  int once_ncg;                 // their 256-column groups
+  size_t db_once_dwp;           // decode_bwd's dW_d partials behind its g_b partials
 
   size_t ws_total;
 };
@@ -279,6 +301,40 @@ inline Plan make_plan(int64_t T, int n, int r) {
     p.eb_gh_off = align_ws((size_t)p.tw_ntg * n * p.RP * 4);
     p.eb_ws = p.eb_gh_off + align_ws((size_t)Tm * r * 4);
   }
+
+  // ---- short streams: never more workspace than the streaming kernels need
+#if !RESBM_IO_F32_BUILD
+  const int64_t jg = ceil_div(p.NT, short_jt(p.NT));
+  for (int mt = 1; mt <= 4 && !p.ef_smt; mt *= 2) {
+    const int64_t blocks = ceil_div(Tm, 16 * mt) * jg;
+    if (mt == 4 ? blocks <= 2 * kNumCU && n * 16 * short_jt(p.NT) <= kEfShortMt4
+                : blocks < kNumCU || (mt == 2 && blocks == kNumCU)) {
+      p.ef_smt = mt;
+      int64_t most = n / 512;            // at least one 64-column unit per wave and slice
+      if (most > n / Tm) most = n / Tm;  // the partials [slices][T][RP] fit the fragments' place
+      p.ef_nsl = (int)clamp64(kNumCU / blocks, 1, most < 1 ? 1 : most);
+    }
+  }
+  // steps per block of the backward ops: as many as leave a block per compute
+  // unit, and enough for the partial sums of the token groups to fit
+  if (Tm * n <= kOnceElems) {
+    const int64_t tiles = ceil_div(Tm, 64);
+    const size_t dw1 = (size_t)p.RP * n * 4;  // one token group's partials
+    p.once_ncg = (int)ceil_div(n, 256);
+    const size_t gb = align_ws((size_t)p.once_ncg * Tm * p.RP * 4);
+    const int64_t fit = p.db_ws > gb ? (int64_t)((p.db_ws - gb) / dw1) : 0;
+    const int64_t per = clamp64(tiles * p.once_ncg * jg / kNumCU, 1, tiles);
+    // (decode_bwd, wide r: a fit of few groups would leave the chip idle)
+    if (fit >= ceil_div(tiles, per) || fit * p.once_ncg * jg >= kNumCU / 2) {
+      p.db_once = (int)(ceil_div(tiles, per) <= fit ? per : ceil_div(tiles, fit));
+      p.db_once_dwp = gb;
+    }
+    if (!p.wide) {
+      const int64_t fe = (int64_t)(p.eb_ws / dw1), pe = clamp64(tiles * p.once_ncg / kNumCU, 1, tiles);
+      p.eb_once = (int)(ceil_div(tiles, pe) <= fe ? pe : ceil_div(tiles, fe));
+    }
+  }
+#endif
 
   size_t m = p.ef_ws;
   if (p.db_ws > m) m = p.db_ws;
