@@ -353,10 +353,12 @@ int32_t resbm_ffn_encode_fwd(int64_t T, int32_t d_ff, int32_t n, int32_t r, int3
  * normalisation (gain gamma) and the QKV projection:
  *     out = RMSNorm(z~) W_qkv,
  *     RMSNorm(x)[t][c] = x[t][c] / sqrt(mean_c' x[t][c']^2 + eps) gamma[c].
- * z~ is never written: every 256 x 256 output tile rebuilds its rows of z~
- * (b W_d, W_d as hi + lo bf16 parts, times gamma, rounded to bf16) for each
- * 64-deep stage of the projection, and the row scale comes from the float32
- * z~ of the same rebuild.  A caller that also needs z~ (its residual stream)
+ * Neither z~ nor its normalised rows are written: the row scale and gamma are
+ * linear factors, so out[t] = s_t b[t] (W_d diag(gamma) W_qkv), with the r x N
+ * matrix formed in the call (W_d gamma and it as hi + lo bf16 parts, float32
+ * sums) and s_t = 1 / sqrt(mean z~[t]^2 + eps) from the float32 z~.  An infinite
+ * gamma or W_qkv entry may give NaN where the sum over c would give an infinity.
+ * A caller that also needs z~ (its residual stream)
  * still runs resbm_decode_fwd.
  *  b      T x r bf16 packed (the payload).
  *  W_d    r x n float32 row-major.   gamma  n float32.
@@ -364,7 +366,7 @@ int32_t resbm_ffn_encode_fwd(int64_t T, int32_t d_ff, int32_t n, int32_t r, int3
  *  out    T x N bf16, row stride ld_out (ld_out >= N, ld_out % 8 == 0).
  * Shape rules: n % 64 == 0, 64 <= n <= 65536; r % 8 == 0, 8 <= r <= 64;
  * N % 8 == 0, 8 <= N <= 262144; eps >= 0.  Pointers 16-byte aligned.  ws: at
- * least resbm_decode_qkv_workspace_bytes(n, r) bytes (W_d in fragment order),
+ * least resbm_decode_qkv_workspace_bytes(n, r) bytes (row sums, W_d in fragment order),
  * 256-byte aligned, caller-owned, dead after the call.
  */
 size_t resbm_decode_qkv_workspace_bytes(int32_t n, int32_t r);

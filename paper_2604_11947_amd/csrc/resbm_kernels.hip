@@ -311,18 +311,6 @@ __device__ __forceinline__ XFrag tr_frag_wide(const io_t* tile, int row0, int c0
   return f;
 }
 
-// Output-column permutation of the "expand" contractions (decode_fwd, the g_z
-// part of encode_bwd).  A wave's A operand covers 16*CT columns starting at c0;
-// row i of column tile ct stands for column
-//     c0 + 32 (ct / 2) + W grp + 4 (ct % 2) + i % 4,   grp = i / 4, W = 8 (CT >= 2) or 4,
-// so that lane group grp ends up holding runs of W consecutive columns and the
-// four lane groups of one token cover 4W contiguous columns per store.
-template <int CT>
-__device__ __forceinline__ int expand_col(int c0, int ct, int i) {
-  constexpr int W = CT >= 2 ? 8 : 4;
-  return c0 + 32 * (ct >> 1) + W * (i >> 2) + 4 * (ct & 1) + (i & 3);
-}
-
 // ============================================================ encode forward
 // Fragment-ordered hi/lo copy of W_e for the A operand of a = z W_e:
 // fragment f = ks * NT + nt, lane (row16, grp) holds W_e[32 ks + 8 grp + e][16 nt + row16].
@@ -1003,23 +991,6 @@ __device__ __forceinline__ void gh_put4(GhTile<TS, RPS>& t, int row, int col, co
   *reinterpret_cast<uint2*>(&t.hi[row][c]) = __builtin_bit_cast(uint2, h);
   *reinterpret_cast<uint2*>(&t.lo[row][c]) = __builtin_bit_cast(uint2, l);
 #endif
-}
-
-// Transposed 16-bit fragment from a plane with PITCH elements per row in the
-// lds_col<PITCH> layout: lane (row16, grp) receives plane[row0 + 8 grp + e][c0 + row16],
-// e = 0..7 (two ds_read_b64_tr_b16, addressed as in tr_frag).
-template <int PITCH>
-__device__ __forceinline__ bf16x8 tr_plane(const __bf16* plane, int row0, int c0, int row16, int grp) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  s16x4 h[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int row = row0 + 8 * grp + 4 * q + (row16 >> 2);
-    const __bf16* p = plane + row * PITCH + lds_col<PITCH>(row, c0 + 4 * (row16 & 3));
-    h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
-  }
-  return __builtin_bit_cast(bf16x8, (short __attribute__((ext_vector_type(8)))){h[0][0], h[0][1], h[0][2], h[0][3],
-                                                                               h[1][0], h[1][1], h[1][2], h[1][3]});
 }
 
 // g_h[row0 + 8 grp + e][c0 + row16] as the A operand of dW_e (k = t).

@@ -60,6 +60,8 @@ struct XFrag { bf16x8 v; };
 struct SFrag { bf16x8 hi, lo; };
 #endif
 
+struct SFragB { bf16x8 hi, lo; };  // the split form of the bf16 build, for ops that are bf16 in both
+
 __device__ __forceinline__ XFrag xfrag_zero() {
   XFrag f;
 #if RESBM_IO_F32_BUILD
@@ -265,6 +267,36 @@ __device__ __forceinline__ int lds_col(int row, int col) {
   } else {
     return tile_col<W>(row, col);
   }
+}
+
+// Transposed 16-bit fragment from a plane with PITCH elements per row in the
+// lds_col<PITCH> layout: lane (row16, grp) receives plane[row0 + 8 grp + e][c0 + row16],
+// e = 0..7: two ds_read_b64_tr_b16, each of which hands lane i of a 16-lane group
+// element i % 4 of the 8-byte chunks addressed by group lanes 4 e + i / 4, e = 0..3.
+template <int PITCH>
+__device__ __forceinline__ bf16x8 tr_plane(const __bf16* plane, int row0, int c0, int row16, int grp) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  s16x4 h[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int row = row0 + 8 * grp + 4 * q + (row16 >> 2);
+    const __bf16* p = plane + row * PITCH + lds_col<PITCH>(row, c0 + 4 * (row16 & 3));
+    h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+  }
+  return __builtin_bit_cast(bf16x8, (short __attribute__((ext_vector_type(8)))){h[0][0], h[0][1], h[0][2], h[0][3],
+                                                                               h[1][0], h[1][1], h[1][2], h[1][3]});
+}
+
+// Output-column permutation of the "expand" contractions (decode_fwd, the g_z
+// part of encode_bwd).  A wave's A operand covers 16*CT columns starting at c0;
+// row i of column tile ct stands for column
+//     c0 + 32 (ct / 2) + W grp + 4 (ct % 2) + i % 4,   grp = i / 4, W = 8 (CT >= 2) or 4,
+// so that lane group grp ends up holding runs of W consecutive columns and the
+// four lane groups of one token cover 4W contiguous columns per store.
+template <int CT>
+__device__ __forceinline__ int expand_col(int c0, int ct, int i) {
+  constexpr int W = CT >= 2 ? 8 : 4;
+  return c0 + 32 * (ct >> 1) + W * (i >> 2) + 4 * (ct & 1) + (i & 3);
 }
 
 // Activation function and its derivative (float32).

@@ -108,7 +108,7 @@ __device__ __forceinline__ int tr_col(int row, int col) {
 }
 
 // Column permutation of a K-contiguous [I][64] tile: the chunk index is XORed
-// with (row / 2) % 8.  dma_tile inverts it when it stages such a tile.
+// with (row / 2) % 8.
 __device__ __forceinline__ int kc_col(int row, int col) {
   return ((((col >> 3) ^ (row >> 1)) & 7) << 3) | (col & 7);
 }
@@ -191,39 +191,6 @@ struct Operand {
     }
   }
 };
-
-// Direct-to-LDS staging of one operand tile (buffer loads with the LDS
-// destination): wave w of NW moves the 1 KiB blocks p NW + w of the tile, lane l
-// filling bytes [16 l, 16 l + 16) of its block, so each lane fetches the chunk
-// whose swizzled position that is (both swizzles are XORs, their own inverse).
-// Out-of-range chunks are fetched at kOOB and land as zeros.
-template <bool KC, int I, int NW>
-__device__ __forceinline__ void dma_tile(rsrc_t src, int64_t ld, int i0, int NI, int k0, int kend, __bf16* tile,
-                                         int wave, int lane) {
-  static_assert(KC || I % 128 == 0, "direct staging of a k-major tile needs rows of a multiple of 128");
-  constexpr int BLOCKS = I * KT * 2 / 1024;
-  static_assert(BLOCKS % NW == 0, "tile blocks must divide over the waves");
-#pragma unroll
-  for (int p = 0; p < BLOCKS / NW; ++p) {
-    const int blk = p * NW + wave;
-    const int o = blk * 1024 + lane * 16;
-    int idx, k;
-    if constexpr (KC) {
-      const int row = o >> 7, pc = (o >> 4) & 7;
-      idx = i0 + row;
-      k = k0 + 8 * ((pc ^ (row >> 1)) & 7);  // kc_col's XOR
-    } else {
-      const int row = o / (I * 2), pc = (o >> 4) % (I / 8);
-      const int f = ((row & 3) | ((row >> 1) & 4)) << 1;  // tr_col's XOR
-      k = k0 + row;
-      idx = i0 + 8 * (((pc ^ f) & 15) | (pc & ~15));
-    }
-    const bool ok = idx < NI && k < kend;
-    const int64_t off = KC ? ((int64_t)idx * ld + k) * 2 : ((int64_t)k * ld + idx) * 2;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)(tile + blk * 512), 16,
-                                             ok ? (uint32_t)off : kOOB, 0, 0, 0);
-  }
-}
 
 // Block index -> tile index.  Consecutive blocks are dispatched to the eight
 // XCDs in turn; each XCD is given a contiguous range of tiles, and tile indices
@@ -949,171 +916,324 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------- decoder into RMSNorm + QKV
+// out = RMSNorm(b W_d) W_qkv.  RMSNorm scales rows of b W_d and its columns (by
+// gamma), so with s_t the row scale
+//     out[t] = s_t (b[t] W_d diag(gamma)) W_qkv = s_t b[t] M,   M = W_d diag(gamma) W_qkv  (r x N):
+// contracting the weights first takes 2 r (n N + T N) operations instead of
+// 2 T n N, and the T x n rows of z~ gamma are never rounded to bf16.  What is
+// left is one read of W_qkv and one write of out (1024 x 4096 x 6144, r = 32:
+// 63 MB).  M is formed again in every call, strip by strip, in the blocks that
+// use it; the row scales come from z~ itself, in float32.
 struct DqArgs {
   int T, n, N, r;
   const __bf16* b;       // T x r
-  const __bf16* wdf;     // W_d fragments (k_frag_prep)
+  const float* W_d;      // r x n
   const float* gamma;    // n
   const __bf16* W;       // n x N, row-major
   int64_t w_bytes;
+  float* ssq;            // [ncg][T] sums of squares of z~ over groups of `cols` columns
+  int ncg, cols;         // cols a multiple of 512
+  __bf16* wf;            // W_d diag(gamma), hi and lo fragments of the first npre 64-row units
+  int npre;
   __bf16* out;           // T x N, row stride ld_out
   int64_t ld_out, out_bytes;
   float eps;
+  int rows;              // rows of out per block (a multiple of 16)
 };
+constexpr int kScRows = 1024;  // row scales held in LDS at a time (a multiple of 256)
 
-// out = RMSNorm(b W_d) W_qkv on 256 x 256 output tiles (8 waves of 128 x 64,
-// the 64-deep stages of k_gemm).  The A operand of every stage -- 64 columns
-// of z~ for the tile's 256 rows -- is rebuilt in the block instead of read:
-// wave w forms rows [32 w, 32 w + 32) of it as b W_d (W_d hi and lo: two
-// products per 16 x 16 piece and 32-deep k-step of r), multiplies by gamma and
-// rounds to bf16 into the LDS tile; W_qkv streams in as in k_gemm.  Each wave
-// also sums the squares of its rows' float32 z~ over the whole K loop; the row
-// scale 1 / sqrt(mean z~^2 + eps) is applied in the epilogue (RMSNorm is a
-// per-row scale of z~ gamma).  The rebuild costs 2 KS / 4 of the tile's
-// products (W_d as hi + lo, KS = r / 32 rounded up).
-template <int KS>
-__global__ __launch_bounds__(512) void k_dec_qkv(DqArgs g) {
-  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, NW = 8;
-  constexpr int FM = BM / (16 * WM), FN = BN / (16 * WN);
-  __shared__ __attribute__((aligned(16))) __bf16 s_a0[BM * KT], s_a1[BM * KT];
-  __shared__ __attribute__((aligned(16))) __bf16 s_b0[BN * KT], s_b1[BN * KT];
-  __shared__ float s_ssq[BM];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int row16 = lane & 15, grp = lane >> 4;
-  const int wm = wave % WM, wn = wave / WM;
-  const int tiles_n = (g.N + BN - 1) / BN;
-  const int t = xcd_tile(blockIdx.x, gridDim.x);
-  const int m0 = (t / tiles_n) * BM, n0 = (t % tiles_n) * BN;
-  const int nst = g.n / KT;
-  const int nc = g.n / 16;
-
-  const rsrc_t rw = make_rsrc(g.W, g.w_bytes);
-  const rsrc_t rbr = make_rsrc(g.b + (int64_t)m0 * g.r, (int64_t)max(0, min(BM, g.T - m0)) * g.r * 2);
-  const rsrc_t rwd = make_rsrc(g.wdf, (int64_t)KS * nc * 2048);
-  const rsrc_t rg = make_rsrc(g.gamma, (int64_t)g.n * 4);
-
-  // b rows of this wave's rebuild (the A slot: lane holds b[row][32 ks + 8 grp + e])
-  bf16x8 bfr[2][KS];
+// W_d[j][k .. k + 7] gamma[k .. k + 7] (zeros at rows >= r) as hi + lo parts: the
+// operand of M, lane (row16, grp) with j = 16 jt + row16, k = k0 + 8 grp.
+__device__ __forceinline__ resbm::SFragB wd_gamma(const DqArgs& g, int j, int k) {
+  float w[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (j < g.r) {
+    const float4* p = reinterpret_cast<const float4*>(g.W_d + (int64_t)j * g.n + k);
+    const float4* q = reinterpret_cast<const float4*>(g.gamma + k);
+    const float4 a = p[0], b = p[1], x = q[0], y = q[1];
+    w[0] = a.x * x.x; w[1] = a.y * x.y; w[2] = a.z * x.z; w[3] = a.w * x.w;
+    w[4] = b.x * y.x; w[5] = b.y * y.y; w[6] = b.z * y.z; w[7] = b.w * y.w;
+  }
+  resbm::SFragB f;
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int e = 0; e < 8; ++e) {
+    __bf16 h, l;
+    resbm::split_hi_lo(w[e], h, l);
+    f.hi[e] = h;
+    f.lo[e] = l;
+  }
+  return f;
+}
+
+// What k_qkv_strip needs of W_d.  blockIdx.y < ncg: sums of squares of z~ over
+// one column group for 64 tokens (a wave takes 64 columns at a time, W_d as hi
+// and lo: two products).  blockIdx.y == ncg: the fragments, a wave each
+// (fragment f = (2 unit + ks) 2 KS + jt: 1 KiB of hi parts, 1 KiB of lo parts).
+template <int KS>
+__global__ __launch_bounds__(512) void k_qkv_prep(DqArgs g) {
+  constexpr int JT = 2 * KS;
+  __shared__ float s_q[8][64];
+  const int lane = threadIdx.x & 63, row16 = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.y == g.ncg) {
+    for (int f = blockIdx.x * 8 + wave; f < g.npre * 2 * JT; f += gridDim.x * 8) {
+      const resbm::SFragB w = wd_gamma(g, 16 * (f % JT) + row16, 32 * (f / JT) + 8 * grp);
+      reinterpret_cast<bf16x8*>(g.wf)[(int64_t)(2 * f) * 64 + lane] = w.hi;
+      reinterpret_cast<bf16x8*>(g.wf)[(int64_t)(2 * f + 1) * 64 + lane] = w.lo;
+    }
+    return;
+  }
+  const int t0 = blockIdx.x * 64;
+  const rsrc_t rb = make_rsrc(g.b + (int64_t)t0 * g.r, (int64_t)min(64, g.T - t0) * g.r * 2);
+  bf16x8 bf[4][KS];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int row = 32 * wave + 16 * rb + row16, j = 32 * ks + 8 * grp;
-      bfr[rb][ks] = __builtin_bit_cast(bf16x8, bld16(rbr, j < g.r ? (uint32_t)((row * g.r + j) * 2) : kOOB));
+      const int j = 32 * ks + 8 * grp;
+      bf[mt][ks] = __builtin_bit_cast(
+          bf16x8, bld16(rb, j < g.r ? (uint32_t)(((16 * mt + row16) * g.r + j) * 2) : kOOB));
     }
-  // W_d fragments and gamma of a stage, loaded one stage ahead
-  struct Wd {
-    bf16x8 hi[4][KS], lo[4][KS];
-    float4 gm[4];
-  };
-  auto load_wd = [&](Wd& w, int s) {
-    const bool ok = s < nst;
+  float q[4] = {0.f, 0.f, 0.f, 0.f};
+  const int cend = min(g.n, ((int)blockIdx.y + 1) * g.cols);
+  for (int c0 = blockIdx.y * g.cols + 64 * wave; c0 < cend; c0 += 512) {
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-      const int c16 = (s * KT) / 16 + cb;
+    for (int ct = 0; ct < 4; ++ct) {
+      resbm::SFragB w[KS];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int64_t f = (int64_t)ks * nc + c16;
-        w.hi[cb][ks] = __builtin_bit_cast(bf16x8, bld16(rwd, ok ? (uint32_t)(((2 * f) * 64 + lane) * 16) : kOOB));
-        w.lo[cb][ks] = __builtin_bit_cast(bf16x8, bld16(rwd, ok ? (uint32_t)(((2 * f + 1) * 64 + lane) * 16) : kOOB));
-      }
-      const uint4 gv = bld16(rg, ok ? (uint32_t)((s * KT + 16 * cb + 4 * grp) * 4) : kOOB);
-      w.gm[cb] = make_float4(__builtin_bit_cast(float, gv.x), __builtin_bit_cast(float, gv.y),
-                             __builtin_bit_cast(float, gv.z), __builtin_bit_cast(float, gv.w));
-    }
-  };
-  float ssq[2] = {0.f, 0.f};
-  // z~ gamma for the stage's 64 columns and the wave's 32 rows, into the A tile
-  auto rebuild = [&](const Wd& w, __bf16* a) {
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+        for (int e = 0; e < 8; ++e) {
+          const int j = 32 * ks + 8 * grp + e, c = c0 + 16 * ct + row16;  // n % 64 == 0: c < n
+          __bf16 h, l;
+          resbm::split_hi_lo(j < g.r ? g.W_d[(int64_t)j * g.n + c] : 0.0f, h, l);
+          w[ks].hi[e] = h;
+          w[ks].lo[e] = l;
+        }
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
+      for (int mt = 0; mt < 4; ++mt) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.hi[cb][ks], bfr[rb][ks], acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.lo[cb][ks], bfr[rb][ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks].lo, bf[mt][ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks].hi, bf[mt][ks], acc, 0, 0, 0);
         }
-        // lane (row16, grp): z~[row][16 cb + 4 grp + v]
-        const float gv[4] = {w.gm[cb].x, w.gm[cb].y, w.gm[cb].z, w.gm[cb].w};
-        bf16x4 h;
+        // lane (row16, grp): z~[t0 + 16 mt + row16][c0 + 16 ct + 4 grp + v]
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          ssq[rb] = fmaf(acc[v], acc[v], ssq[rb]);
-          h[v] = (__bf16)(acc[v] * gv[v]);
-        }
-        const int row = 32 * wave + 16 * rb + row16;
-        *reinterpret_cast<uint2*>(a + tile_pos<true, BM>(row, 16 * cb + 4 * grp)) = __builtin_bit_cast(uint2, h);
+        for (int v = 0; v < 4; ++v) q[mt] = fmaf(acc[v], acc[v], q[mt]);
       }
-  };
-
-  f32x4 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto products_kk = [&](const __bf16* ta, const __bf16* tb, int kk) {
-    bf16x8 fa[FM], fb[FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) fa[i] = frag<true, BM>(ta, (wm * FM + i) * 16, kk, row16, grp);
-#pragma unroll
-    for (int j = 0; j < FN; ++j) fb[j] = frag<false, BN>(tb, (wn * FN + j) * 16, kk, row16, grp);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-  };
-
-  Wd wd;
-  load_wd(wd, 0);
-  // stage 0: its A tile and the B tile
-  rebuild(wd, s_a0);
-  load_wd(wd, 1);
-  dma_tile<false, BN, NW>(rw, g.N, n0, g.N, 0, g.n, s_b0, wave, lane);
-  auto step = [&](int s, const __bf16* a, const __bf16* b, __bf16* na, __bf16* nb) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (s + 1 < nst) {
-      dma_tile<false, BN, NW>(rw, g.N, n0, g.N, (s + 1) * KT, g.n, nb, wave, lane);
-      rebuild(wd, na);
-      load_wd(wd, s + 2);
     }
-    products_kk(a, b, 0);
-    products_kk(a, b, 1);
-  };
-  for (int s = 0; s < nst; s += 2) {
-    step(s, s_a0, s_b0, s_a1, s_b1);
-    if (s + 1 < nst) step(s + 1, s_a1, s_b1, s_a0, s_b0);
   }
-
-  // row sums of squares: the four lane groups of a row, then one writer per row
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    float v = ssq[rb];
+  for (int mt = 0; mt < 4; ++mt) {
+    float v = q[mt];
     v += __shfl_xor(v, 16);
     v += __shfl_xor(v, 32);
-    if (grp == 0) s_ssq[32 * wave + 16 * rb + row16] = v;
+    if (grp == 0) s_q[wave][16 * mt + row16] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 64 && t0 + (int)threadIdx.x < g.T) {
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += s_q[w][threadIdx.x];
+    g.ssq[(int64_t)blockIdx.y * g.T + t0 + threadIdx.x] = v;
+  }
+}
+
+// Columns [16 CT blockIdx.x, ...) of out for g.rows tokens.  The 8 waves take
+// the 64-row units of W_qkv in turn: a unit goes through the wave's own LDS
+// tile and is read back transposed, W_d gamma (hi and lo: two products) comes
+// from the cache in fragment order (or, behind the units that the workspace
+// holds, is split here); the next two units' loads are in flight meanwhile.  The waves' parts of M meet in LDS in wave order and are kept
+// there as hi and lo planes; then the waves take 32-row tiles of out in turn.
+// Against the 256 x 256 tiles that rebuilt z~ gamma per stage: 158 -> 37.5 us at
+// 1024 x 4096 x 6144, r = 32, and 973 -> 94 at 16384 rows.  What bounds it: the
+// latency of W_qkv's 64-row units (8 per wave) at few rows, the writes of out at many.
+// (Splitting W_d gamma in every block instead of reading fragments: 43.8 us.)
+template <int KS, int CT>
+__global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
+  constexpr int KP = 32 * KS, JT = 2 * KS, WC = 16 * CT, LPR = WC / 8, RPI = 64 / LPR, NQ = 64 / RPI;
+  constexpr int STAGE = 8 * 64 * WC * 2, PP = KP + 4, PART = 8 * WC * PP * 4;
+  __shared__ __attribute__((aligned(16))) char smem[STAGE > PART ? STAGE : PART];
+  __shared__ __attribute__((aligned(16))) __bf16 s_m[2][WC * KP];
+  __shared__ float s_sc[kScRows];
+  const int lane = threadIdx.x & 63, row16 = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = xcd_tile(blockIdx.x, gridDim.x) * WC, nu = g.n / 64;
+  __bf16* const tile = reinterpret_cast<__bf16*>(smem) + wave * 64 * WC;
+  const rsrc_t rw = make_rsrc(g.W, g.w_bytes), rf = make_rsrc(g.wf, (int64_t)g.npre * 4 * JT * 1024);
+  const int wrow = lane / LPR, wcol = 8 * (lane % LPR);
+  const bool con = c0 + wcol < g.N;
+
+  // scales of the rows [ts, ts + kScRows) of the block's range
+  const int tb = blockIdx.y * g.rows, te = min(g.T, tb + g.rows);
+  const float inv_n = 1.0f / (float)g.n;
+  auto row_scales = [&](int ts) {
+    for (int i = threadIdx.x; i < kScRows && ts + i < te; i += 512) {
+      float q = 0.0f;
+      for (int k = 0; k < g.ncg; ++k) q += g.ssq[(int64_t)k * g.T + ts + i];
+      s_sc[i] = 1.0f / sqrtf(q * inv_n + g.eps);
+    }
+  };
+
+  uint4 wa[NQ], wb[NQ], dq[2][JT][2];
+  auto load_w = [&](uint4 (&wq)[NQ], int u) {
+    const bool on = u < nu;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      wq[q] = bld16<2>(rw, on && con ? (uint32_t)(((int64_t)(64 * u + q * RPI + wrow) * g.N + c0 + wcol) * 2) : kOOB);
+  };
+  auto load_d = [&](int u) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          dq[ks][jt][p] = bld16(rf, u < g.npre ? (uint32_t)(((((2 * u + ks) * JT + jt) * 2 + p) * 64 + lane) * 16) : kOOB);
+  };
+  f32x4 acc[JT][CT];
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[jt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // unit u, its rows of W_qkv in wq (reloaded with those of the unit after next;
+  // issued behind the next unit's W_d, so that the wait for those leaves them in flight)
+  auto unit = [&](uint4 (&wq)[NQ], int u) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int row = q * RPI + wrow;
+      *reinterpret_cast<uint4*>(tile + row * WC + resbm::lds_col<WC>(row, wcol)) = wq[q];
+    }
+    resbm::SFragB d[2][JT];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        if (u < g.npre) {
+          d[ks][jt].hi = __builtin_bit_cast(bf16x8, dq[ks][jt][0]);
+          d[ks][jt].lo = __builtin_bit_cast(bf16x8, dq[ks][jt][1]);
+        } else {
+          d[ks][jt] = wd_gamma(g, 16 * jt + row16, 64 * u + 32 * ks + 8 * grp);
+        }
+      }
+    load_d(u + 8);
+    load_w(wq, u + 16);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wave's own tile is complete
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const bf16x8 w = resbm::tr_plane<WC>(tile, 32 * ks, 16 * ct, row16, grp);
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt) {
+          acc[jt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[ks][jt].lo, w, acc[jt][ct], 0, 0, 0);
+          acc[jt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[ks][jt].hi, w, acc[jt][ct], 0, 0, 0);
+        }
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the next unit overwrites it
+  };
+  load_w(wa, wave);
+  load_d(wave);
+  load_w(wb, wave + 8);
+  row_scales(tb);  // (read behind the barriers below)
+  for (int u = wave; u < nu; u += 16) {
+    unit(wa, u);
+    if (u + 8 < nu) unit(wb, u + 8);
+  }
+  __syncthreads();  // the parts overlap the tiles
+  // lane (row16, grp): part of M[16 jt + 4 grp + v][c0 + 16 ct + row16]
+  float* const part = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      *reinterpret_cast<float4*>(part + (wave * WC + 16 * ct + row16) * PP + 16 * jt + 4 * grp) =
+          make_float4(acc[jt][ct][0], acc[jt][ct][1], acc[jt][ct][2], acc[jt][ct][3]);
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < WC * KP / 4; idx += 512) {
+    const int c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+      const float4 p = *reinterpret_cast<const float4*>(part + (w * WC + c) * PP + j);
+      m[0] += p.x; m[1] += p.y; m[2] += p.z; m[3] += p.w;
+    }
+    bf16x4 h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      __bf16 a, b;
+      resbm::split_hi_lo(m[e], a, b);
+      h[e] = a;
+      l[e] = b;
+    }
+    const int pos = c * KP + resbm::tile_col<KP>(c, j);
+    *reinterpret_cast<uint2*>(&s_m[0][pos]) = __builtin_bit_cast(uint2, h);
+    *reinterpret_cast<uint2*>(&s_m[1][pos]) = __builtin_bit_cast(uint2, l);
   }
   __syncthreads();
 
-  const rsrc_t ro = make_rsrc(g.out, g.out_bytes);
-  const float inv_n = 1.0f / (float)g.n;
+  // M as the first operand: row i of tile ct is column expand_col(ct, i), so that
+  // a lane ends up with runs of 8 consecutive columns
+  resbm::SFragB m[CT][KS];
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int ml = (wm * FM + i) * 16 + row16;
-    const int m = m0 + ml;
-    const float sc = 1.0f / sqrtf(s_ssq[ml] * inv_n + g.eps);
+  for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = n0 + (wn * FN + j) * 16 + 4 * grp;
-      const bool ok = m < g.T && n < g.N;
-      bf16x4 h;
+    for (int ks = 0; ks < KS; ++ks) {
+      const int c = resbm::expand_col<CT>(0, ct, row16), pos = c * KP + resbm::tile_col<KP>(c, 32 * ks + 8 * grp);
+      m[ct][ks].hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&s_m[0][pos]));
+      m[ct][ks].lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&s_m[1][pos]));
+    }
+  const rsrc_t rb = make_rsrc(g.b, (int64_t)g.T * g.r * 2), ro = make_rsrc(g.out, g.out_bytes);
+  bf16x8 bn[2][KS];
+  auto load_b = [&](int t) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) h[e] = (__bf16)(acc[i][j][e] * sc);
-      bst8(ro, ok ? (uint32_t)(((int64_t)m * g.ld_out + n) * 2) : kOOB, __builtin_bit_cast(uint2, h));
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int j = 32 * ks + 8 * grp, tp = t + 16 * p;
+        bn[p][ks] =
+            __builtin_bit_cast(bf16x8, bld16(rb, tp < te && j < g.r ? (uint32_t)(((int64_t)tp * g.r + j) * 2) : kOOB));
+      }
+  };
+  for (int ts = tb; ts < te; ts += kScRows) {
+    if (ts > tb) {
+      __syncthreads();  // the scales of the rows before are used up
+      row_scales(ts);
+      __syncthreads();
+    }
+    const int tl = min(te, ts + kScRows);
+    load_b(ts + 32 * wave + row16);
+    for (int t0 = ts + 32 * wave; t0 < tl; t0 += 256) {
+      bf16x8 bv[2][KS];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) bv[p][ks] = bn[p][ks];
+      load_b(t0 + 256 + row16);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int t = t0 + 16 * p + row16;
+        const float sc = s_sc[t - ts];
+        f32x4 o[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          o[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) {
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m[ct][ks].lo, bv[p][ks], o[ct], 0, 0, 0);
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m[ct][ks].hi, bv[p][ks], o[ct], 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < CT / 2; ++h) {
+          const int c = c0 + 32 * h + 8 * grp;
+          bf16x8 v;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = (__bf16)(o[2 * h + (e >> 2)][e & 3] * sc);
+          bst16(ro, t < te && c < g.N ? (uint32_t)(((int64_t)t * g.ld_out + c) * 2) : kOOB,
+                __builtin_bit_cast(uint4, v));
+        }
+      }
     }
   }
 }
@@ -1325,6 +1445,13 @@ void weight_grad(Shape s, GemmArgs g, const Split& sp, float* W, void* part, hip
                      sp.S, count, W);
 }
 
+template <int KS>
+void launch_qkv(const DqArgs& g, int ct, int ranges, hipStream_t st) {
+  hipLaunchKernelGGL(k_qkv_prep<KS>, dim3((g.T + 63) / 64, g.ncg + 1), dim3(512), 0, st, g);
+  const dim3 grid((g.N + 16 * ct - 1) / (16 * ct), ranges);
+  if (ct == 2) hipLaunchKernelGGL((k_qkv_strip<KS, 2>), grid, dim3(512), 0, st, g);
+  else hipLaunchKernelGGL((k_qkv_strip<KS, 4>), grid, dim3(512), 0, st, g);
+}
 
 int32_t check_ws(size_t need, const void* ws, size_t ws_bytes) {
   if (need == 0) return RESBM_OK;
@@ -1647,20 +1774,42 @@ int32_t resbm_decode_qkv_fwd(int64_t T, int32_t n, int32_t r, int32_t N, const v
     if (overlap(out, bo, ins[i], inb[i]) || overlap(ws, need, ins[i], inb[i])) return RESBM_E_ALIAS;
   if (overlap(out, bo, ws, need)) return RESBM_E_ALIAS;
   hipStream_t st = (hipStream_t)stream;
+  // The workspace holds the sums of squares of a chunk of tokens (at most a
+  // quarter of it: 8 n tokens, 16 n above r = 32) and, behind them, as many units
+  // of W_d's fragments as fit.
   const int KS = (r + 31) / 32;
-  hipLaunchKernelGGL(k_frag_prep, dim3((unsigned)(KS * (n / 16))), dim3(64), 0, st, W_d, r, n, (int64_t)n, n / 16,
-                     (__bf16*)ws);
+  const int64_t most = (int64_t)(need / 16) / 64 * 64;
   DqArgs g{};
-  g.T = (int)T; g.n = n; g.N = N; g.r = r;
-  g.b = (const __bf16*)b; g.wdf = (const __bf16*)ws; g.gamma = gamma;
+  g.n = n; g.N = N; g.r = r;
+  g.W_d = W_d; g.gamma = gamma;
   g.W = (const __bf16*)W_qkv; g.w_bytes = (int64_t)bw;
-  g.out = (__bf16*)out; g.ld_out = ld_out; g.out_bytes = (int64_t)bo;
+  g.ssq = (float*)ws;
+  g.ld_out = ld_out;
   g.eps = eps;
-  const unsigned tiles = (unsigned)(((T + 255) / 256) * ((N + 255) / 256));
-  if (KS == 1)
-    hipLaunchKernelGGL(k_dec_qkv<1>, dim3(tiles), dim3(512), 0, st, g);
-  else
-    hipLaunchKernelGGL(k_dec_qkv<2>, dim3(tiles), dim3(512), 0, st, g);
+  for (int64_t t0 = 0; t0 < T; t0 += most) {
+    g.T = (int)std::min(most, T - t0);
+    g.b = (const __bf16*)b + t0 * r;
+    g.out = (__bf16*)out + t0 * ld_out;
+    g.out_bytes = (int64_t)extent(g.T, N, ld_out, 2);
+    for (g.cols = 512;; g.cols *= 2) {
+      g.ncg = (n + g.cols - 1) / g.cols;
+      if (g.ncg == 1 || (size_t)g.ncg * g.T * 16 <= need) break;
+    }
+    const size_t sq = round_up((size_t)g.ncg * g.T * 4, kWsAlign2);
+    g.wf = (__bf16*)((char*)ws + sq);
+    g.npre = (int)std::min<size_t>(n / 64, (need - sq) / (KS * 8192));
+    // 32-column strips while out is short (more blocks: 37.5 us either way at
+    // 1024 x 4096 x 6144, r = 32; 27.6 against 52.4 at 300 x 2112 x 4000, r = 64);
+    // beyond, 64-column ones write whole 128-byte lines (16384 x 4096 x 6144:
+    // 94 against 113 us; at r = 64 their spills cost more up to 8192 rows)
+    const int ct = g.T <= (KS == 1 ? 2048 : 8192) ? 2 : 4, strips = (N + 16 * ct - 1) / (16 * ct);
+    // token ranges: blocks for the whole chip, one per compute unit (two: 74 against 44 us at 1024 rows)
+    int ranges = std::max(1, std::min(kNumBlocks / strips, (g.T + 255) / 256));
+    g.rows = (int)round_up((size_t)(g.T + ranges - 1) / ranges, 256);
+    ranges = (g.T + g.rows - 1) / g.rows;
+    if (KS == 1) launch_qkv<1>(g, ct, ranges, st);
+    else launch_qkv<2>(g, ct, ranges, st);
+  }
   return resbm_host::launch_status();
 }
 
