@@ -27,9 +27,10 @@
 // Short side s4 <= 64, few steps: the iteration runs on the s x s Gram alone.
 // With X_0 = kappa U and Q_k = a I + b A_k + c A_k^2, X_{k+1} = X_k Q_k, so
 // X_k = X_0 P_k with P_0 = I, P_{k+1} = P_k Q_k, and the next Gram is
-// A_{k+1} = Q_k A_k Q_k (Q_k is a polynomial in the symmetric A_k).  One block
-// (k_mx_small) takes the Gram of U (k_mx_reduce), runs that recurrence in LDS
-// and writes R = kappa P_n; one row pass then forms X_n = U R.  Four launches
+// A_{k+1} = Q_k A_k Q_k (Q_k is a polynomial in the symmetric A_k).  k_ns_gram
+// applies the momentum and writes partial Grams of U; one block (k_ns_small)
+// adds them, runs that recurrence in LDS and writes R = kappa P_n; k_ns_out
+// forms X_n = U R.  Three launches (four with many partials)
 // instead of 1 + 2n.  Equal to the row-by-row iteration in exact arithmetic;
 // in float64 the two agree to ~1e-12 of max |X_n| at the default 5 quintic
 // steps.  A direction of A_0 whose computed eigenvalue is a rounding error
@@ -431,22 +432,20 @@ __global__ __launch_bounds__(kThreads) void k_mx_poly(int s4, const double* A, d
 // ---------------------------------------------------------------- short-side recurrence
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallMax = 64;               // s4 of the short-side recurrence
-constexpr int kSmallLd = kSmallMax + 1;     // padded LDS row stride (doubles)
 
-// Z = X Y for s4 x s4 matrices in LDS (row stride ld, zero beyond s4 up to a
+// Tile w of X Y for matrices in LDS (row stride ld, zero beyond s4 up to a
 // multiple of 16) on the float64 matrix cores: v_mfma_f64_16x16x4_f64 per
-// 16 x 16 tile and 4-deep k-step, one tile per wave.  Lane (row16, grp) holds
-// A[row16][grp] and B[grp][row16]; its accumulator element v is
-// D[grp + 4 v][row16] (measured on gfx950).
+// 4-deep k-step.  Lane (row16, grp) holds A[row16][grp] and B[grp][row16]; its
+// accumulator element v is D[grp + 4 v][row16] (measured on gfx950).
 // NT = tiles per side (s4 <= 16 NT); the k-steps run to 16 NT over the zero
 // padding, all operand loads issued before the products.
 template <int NT>
-__device__ __forceinline__ void small_mm(const double* X, const double* Y, double* Z, int ld) {
+__device__ __forceinline__ double __attribute__((ext_vector_type(4))) small_tile(int w, const double* X,
+                                                                                 const double* Y, int ld) {
   typedef double d4 __attribute__((ext_vector_type(4)));
   constexpr int KSTEPS = 4 * NT;
-  const int l = threadIdx.x & 63, row16 = l & 15, grp = l >> 4, wave = threadIdx.x >> 6;
-  if (wave >= NT * NT) return;  // one tile per wave (16 waves >= NT^2)
-  const int i0 = 16 * (wave / NT), j0 = 16 * (wave % NT);
+  const int l = threadIdx.x & 63, row16 = l & 15, grp = l >> 4;
+  const int i0 = 16 * (w / NT), j0 = 16 * (w % NT);
   double xa[KSTEPS], yb[KSTEPS];
 #pragma unroll
   for (int q = 0; q < KSTEPS; ++q) {
@@ -456,62 +455,245 @@ __device__ __forceinline__ void small_mm(const double* X, const double* Y, doubl
   d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int q = 0; q < KSTEPS; ++q) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[q], yb[q], acc, 0, 0, 0);
+  return acc;
+}
+template <int NT>
+__device__ __forceinline__ void put_tile(int w, const double __attribute__((ext_vector_type(4))) & acc, double* Z,
+                                         int ld) {
+  const int l = threadIdx.x & 63, row16 = l & 15, grp = l >> 4;
+  const int i0 = 16 * (w / NT), j0 = 16 * (w % NT);
 #pragma unroll
   for (int v = 0; v < 4; ++v) Z[(i0 + grp + 4 * v) * ld + j0 + row16] = acc[v];
 }
+// Z = X Y, one tile per wave (16 waves >= NT^2); POLY: Z = a I + b X + c X Y.
+template <int NT, bool POLY>
+__device__ __forceinline__ void small_mm(int wave, const double* X, const double* Y, double* Z, int ld, double a,
+                                         double b, double c, int s4) {
+  if (wave >= NT * NT) return;
+  auto acc = small_tile<NT>(wave, X, Y, ld);
+  if constexpr (POLY) {
+    const int l = threadIdx.x & 63, row16 = l & 15, grp = l >> 4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * (wave / NT) + grp + 4 * v, j = 16 * (wave % NT) + row16;
+      acc[v] = (i == j && i < s4 ? a : 0.0) + b * X[i * ld + j] + c * acc[v];
+    }
+  }
+  put_tile<NT>(wave, acc, Z, ld);
+}
 
-// One block: from the reduced Gram A_0 (s4 x s4, row-major), kappa =
-// 1 / (sqrt(trace A_0) + eps), then n steps of the recurrence on
-// Ab = kappa^2 A_0; writes R = kappa P_n to Rout (s4 x s4, row-major) and 1 to
-// scal[0] (the row pass scales by it).
+// The matrix to orthogonalise at an element, from the gradient and the momentum
+// after its update (momentum_step's result once more, the same roundings).
+__device__ __forceinline__ double updated(const RowArgs& g, double gv, float mn) {
+#pragma clang fp contract(off)
+  return !g.mom ? gv : g.nesterov ? gv + g.mu * (double)mn : (double)mn;
+}
+
+// Partial Gram of the rows [b ch, b ch + ch) of U (momentum applied first when
+// given), 128 rows at a time through LDS.  The 16 waves take the 16 NT x 16 NT
+// tiles of the Gram; with fewer tiles than waves, groups of waves take every
+// G-th 4-row step and meet in LDS in group order.  U itself is not kept: the
+// output pass forms it again from G and M (same values, half the bytes).
+// One round trip to memory and one Gram bound it: 15.0 -> 5.1 us at 4096 x 32
+// against k_mx_rows<kLoad> (vector products, run-time divisions, X written out).
 template <int NT>
-__global__ __launch_bounds__(kSmallThreads) void k_mx_small(int s4, const double* A0, int n, double a, double b,
-                                                            double c, double* Rout, double* scal) {
-  __shared__ double s_a[kSmallMax * kSmallLd], s_p[kSmallMax * kSmallLd];
-  __shared__ double s_q[kSmallMax * kSmallLd], s_t[kSmallMax * kSmallLd];
+__global__ __launch_bounds__(kSmallThreads) void k_ns_gram(Dims d, RowArgs g, int ch) {
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  constexpr int R = 128, W = 16 * NT, LD = W + 1, NW = NT * NT, G = NW <= 1 ? 16 : NW <= 4 ? 4 : 1;
+  constexpr int NE = R * W / kSmallThreads;
+  constexpr int RED = G > 1 ? G * W * W : 0;
+  __shared__ double s_x[RED > R * LD ? RED : R * LD];
+  const int t = threadIdx.x, l = t & 63, row16 = l & 15, grp = l >> 4, wave = t >> 6;
+  const int i0 = 16 * (wave % NW / NT), j0 = 16 * (wave % NT), kg = wave / NW;
+  const int64_t r0 = (int64_t)blockIdx.x * ch, r1 = r0 + ch < d.L ? r0 + ch : d.L;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t t0 = r0; t0 < r1; t0 += R) {
+    float gv[NE], mv[NE];
+    int64_t pi[NE];
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+      const int e = t + q * kSmallThreads;  // in order of the stored layout
+      const int i = d.tall ? e / W : e % R, k = d.tall ? e % W : e / R;
+      pi[q] = t0 + i < r1 && k < d.s ? phys(d, t0 + i, k) : -1;
+      gv[q] = pi[q] >= 0 ? g.src[pi[q]] : 0.0f;
+      mv[q] = pi[q] >= 0 && g.mom ? g.mom[pi[q]] : 0.0f;
+    }
+    if (t0 > r0) __syncthreads();  // the last rows' products are done
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+      const int e = t + q * kSmallThreads;
+      const int i = d.tall ? e / W : e % R, k = d.tall ? e % W : e / R;
+      double u = gv[q];
+      if (g.mom && pi[q] >= 0) {
+        float m = mv[q];
+        u = momentum_step(&m, gv[q], g.mu, g.nesterov);
+        g.mom[pi[q]] = m;
+      }
+      s_x[i * LD + k] = u;
+    }
+    __syncthreads();
+    if (kg < G) {
+#pragma unroll
+      for (int ks = 0; ks < R / 4 / G; ++ks) {
+        const double* x = s_x + (4 * (ks * G + kg) + grp) * LD + row16;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i0], x[j0], acc, 0, 0, 0);
+      }
+    }
+  }
+  double* const part = g.part + (int64_t)blockIdx.x * d.s4 * d.s4;
+  if constexpr (G > 1) {
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_x[kg * W * W + (i0 + grp + 4 * v) * W + j0 + row16] = acc[v];
+    __syncthreads();
+    for (int e = t; e < W * W; e += kSmallThreads) {
+      double v = 0.0;
+#pragma unroll
+      for (int k = 0; k < G; ++k) v += s_x[k * W * W + e];
+      if (e / W < d.s4 && e % W < d.s4) part[e / W * d.s4 + e % W] = v;
+    }
+  } else if (kg < G) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (i0 + grp + 4 * v < d.s4 && j0 + row16 < d.s4) part[(i0 + grp + 4 * v) * d.s4 + j0 + row16] = acc[v];
+  }
+}
+
+// One block: A_0 = the nch partial Grams in order (s4 x s4, row-major; one, when
+// they were reduced before), kappa = 1 / (sqrt(trace A_0) + eps), then n steps of
+// the recurrence on Ab = kappa^2 A_0; writes R = kappa P_n to Rout (s4 x s4,
+// row-major).  Three barriers per step: Q leaves the product A^2 from its
+// accumulators, and P Q runs beside A Q on other waves where both fit.  Bound by
+// the chain of dependent float64 products (14 at five steps): 12.9 us at s = 32
+// with the sum of 32 partials, 15.8 before (reduction 4.6, recurrence 11.2).
+template <int NT>
+__global__ __launch_bounds__(kSmallThreads) void k_ns_small(int s4, const double* part, int nch, int n, double a,
+                                                            double b, double c, double* Rout) {
+  constexpr int LD = 16 * NT + 1, NW = NT * NT;
+  constexpr bool BESIDE = 2 * NW <= 16;
+  __shared__ double s_m[4][16 * NT * LD];
   __shared__ double s_kappa;
-  const int t = threadIdx.x, ld = kSmallLd, ne = s4 * s4;
+  const int t = threadIdx.x, wave = t >> 6, l = t & 63, ne = s4 * s4;
+  double* A = s_m[0];
+  double* P = s_m[1];
+  double* U = s_m[2];
+  double* const Q = s_m[3];
   // the matrix-core tiles read up to a multiple of 16 rows and columns: zeros there
-  for (int e = t; e < kSmallMax * kSmallLd; e += kSmallThreads) s_a[e] = s_p[e] = s_q[e] = s_t[e] = 0.0;
-  __syncthreads();
-  for (int e = t; e < ne; e += kSmallThreads) {
-    s_a[(e / s4) * ld + e % s4] = A0[e];
-    s_p[(e / s4) * ld + e % s4] = (e / s4 == e % s4) ? 1.0 : 0.0;
+  for (int e = t; e < 16 * NT * LD; e += kSmallThreads) {
+    const int i = e / LD, j = e % LD;
+    double v = 0.0;
+    if (i < s4 && j < s4) {
+      const double* p = part + i * s4 + j;
+      int k = 0;
+      for (; k + 16 <= nch; k += 16) {
+        double x[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[q] = p[(int64_t)(k + q) * ne];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v += x[q];
+      }
+      for (; k < nch; ++k) v += p[(int64_t)k * ne];
+    }
+    A[e] = v;
+    P[e] = i < s4 && i == j ? 1.0 : 0.0;
   }
   __syncthreads();
-  if (t == 0) {
-    double tr = 0.0;
-    for (int i = 0; i < s4; ++i) tr += s_a[i * ld + i];
-    s_kappa = 1.0 / (sqrt(tr) + kNsEps);
+  if (wave == 0) {
+    double tr = l < s4 ? A[l * LD + l] : 0.0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) tr += __shfl_xor(tr, o);
+    if (l == 0) s_kappa = 1.0 / (sqrt(tr) + kNsEps);
   }
   __syncthreads();
   const double kappa = s_kappa, k2 = kappa * kappa;
-  for (int e = t; e < ne; e += kSmallThreads) s_a[(e / s4) * ld + e % s4] *= k2;
+  for (int e = t; e < 16 * NT * LD; e += kSmallThreads) A[e] *= k2;
   __syncthreads();
-  double* P = s_p;  // P_k and a scratch matrix swap roles after every P Q
-  double* U = s_t;
   for (int k = 0; k < n; ++k) {
-    small_mm<NT>(s_a, s_a, s_q, ld);  // A^2
+    small_mm<NT, true>(wave, A, A, Q, LD, a, b, c, s4);  // Q = a I + b A + c A^2
     __syncthreads();
-    for (int e = t; e < ne; e += kSmallThreads) {
-      const int i = e / s4, j = e % s4;
-      s_q[i * ld + j] = (i == j ? a : 0.0) + b * s_a[i * ld + j] + c * s_q[i * ld + j];  // Q
-    }
-    __syncthreads();
-    small_mm<NT>(P, s_q, U, ld);  // P Q
-    __syncthreads();
-    double* w = P;
-    P = U;
-    U = w;
+    small_mm<NT, false>(wave, P, Q, U, LD, 0.0, 0.0, 0.0, s4);  // P Q
+    double* const AQ = P;  // free once P Q is formed
     if (k + 1 < n) {
-      small_mm<NT>(s_a, s_q, U, ld);  // A Q
+      if constexpr (BESIDE) {
+        // (P is still being read: A Q goes to registers first)
+        typedef double d4 __attribute__((ext_vector_type(4)));
+        const int w = wave - NW;
+        d4 acc = {0.0, 0.0, 0.0, 0.0};
+        if (w >= 0 && w < NW) acc = small_tile<NT>(w, A, Q, LD);
+        __syncthreads();
+        if (w >= 0 && w < NW) put_tile<NT>(w, acc, AQ, LD);
+      } else {
+        __syncthreads();
+        small_mm<NT, false>(wave, A, Q, AQ, LD, 0.0, 0.0, 0.0, s4);
+      }
       __syncthreads();
-      small_mm<NT>(s_q, U, s_a, ld);  // next A = Q (A Q)
-      __syncthreads();
+      small_mm<NT, false>(wave, Q, AQ, A, LD, 0.0, 0.0, 0.0, s4);  // next A = Q (A Q)
     }
+    __syncthreads();
+    P = U;
+    U = AQ;
   }
-  for (int e = t; e < ne; e += kSmallThreads) Rout[e] = kappa * P[(e / s4) * ld + e % s4];
-  if (t == 0) scal[0] = 1.0;
+  for (int e = t; e < ne; e += kSmallThreads) Rout[e] = kappa * P[(e / s4) * LD + e % s4];
+}
+
+// X_n = U R for 16 logical rows per wave, R from k_ns_small; outputs as put_rows.
+// The operands are swapped for a wide matrix, so that 16 lanes write consecutive
+// elements of the stored layout either way.  Three dependent memory round trips
+// bound it: 5.9 us at 4096 x 32, 8.9 at 32 x 4096 (64-byte segments of 32 rows),
+// with k_mx_rows<kOutW> 7.6; the whole update 39.8 -> 24.2 us and 40.5 -> 26.
+template <int NT, int MODE, bool TALL>
+__global__ __launch_bounds__(64) void k_ns_out(Dims d, RowArgs g, const double* Rm) {
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  constexpr int KS = 4 * NT;
+  const int l = threadIdx.x, row16 = l & 15, grp = l >> 4;
+  const int64_t l0 = (int64_t)blockIdx.x * 16;
+  const bool lon = l0 + row16 < d.L;
+  float gv[KS], mv[KS];
+#pragma unroll
+  for (int q = 0; q < KS; ++q) {
+    const int k = 4 * q + grp;
+    const bool ok = lon && k < d.s;
+    const int64_t pi = ok ? phys(d, l0 + row16, k) : 0;
+    gv[q] = ok && (!g.mom || g.nesterov) ? g.src[pi] : 0.0f;
+    mv[q] = ok && g.mom ? g.mom[pi] : 0.0f;
+  }
+  int64_t pi[NT][4];
+  float w[NT][4];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * nt + (TALL ? row16 : grp + 4 * v);
+      const int64_t lr = l0 + (TALL ? grp + 4 * v : row16);
+      pi[nt][v] = lr < d.L && k < d.s ? phys(d, lr, k) : -1;
+      w[nt][v] = MODE == kOutW && pi[nt][v] >= 0 ? g.out[pi[nt][v]] : 0.0f;
+    }
+  double u[KS];
+#pragma unroll
+  for (int q = 0; q < KS; ++q) u[q] = updated(g, gv[q], mv[q]);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    double r[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      const int k = 4 * q + grp, j = 16 * nt + row16;
+      r[q] = k < d.s4 && j < d.s4 ? Rm[k * d.s4 + j] : 0.0;
+    }
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < KS; ++q)
+      acc = TALL ? __builtin_amdgcn_mfma_f64_16x16x4f64(u[q], r[q], acc, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f64_16x16x4f64(r[q], u[q], acc, 0, 0, 0);
+    float o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const double x = w[nt][v];
+      o[v] = (float)(MODE == kOutW ? x - g.lr * (g.scale * acc[v] + g.wd * x) : acc[v]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (pi[nt][v] >= 0) g.out[pi[nt][v]] = o[v];
+  }
 }
 
 // Whether the short-side recurrence applies: s4 <= 64 and |a|^(2n) <= 1e9.
@@ -810,6 +992,31 @@ int32_t check_ws(const Plan& P, const void* ws, size_t ws_bytes) {
   return RESBM_OK;
 }
 
+// The short-side recurrence (s4 <= 64).  Chunks of at least 128 rows, at most
+// d.nch of them (the workspace's partial Grams).  k_ns_small adds the partials
+// itself up to 512 KiB of them (one compute unit reads that in the time of the
+// launch it saves); beyond, k_mx_reduce does.
+template <int NT, int MODE_OUT>
+void run_small(const Dims& d, const RowArgs& g, double* A, double* R, int n, double a, double b, double c,
+               hipStream_t st) {
+  const int ne = d.s4 * d.s4;
+  int nch = (d.L + 127) / 128;
+  nch = nch < d.nch ? nch : d.nch;
+  const int ch = (d.L + nch - 1) / nch;
+  nch = (d.L + ch - 1) / ch;
+  hipLaunchKernelGGL(k_ns_gram<NT>, dim3(nch), dim3(kSmallThreads), 0, st, d, g, ch);
+  const bool own = (int64_t)nch * ne <= 65536;
+  if (!own)
+    hipLaunchKernelGGL(k_mx_reduce, dim3((ne + kThreads - 1) / kThreads), dim3(kThreads), 0, st, ne, nch,
+                       (const double*)g.part, A);
+  hipLaunchKernelGGL(k_ns_small<NT>, dim3(1), dim3(kSmallThreads), 0, st, d.s4, own ? (const double*)g.part : A,
+                     own ? nch : 1, n, a, b, c, R);
+  if (d.tall)
+    hipLaunchKernelGGL((k_ns_out<NT, MODE_OUT, true>), dim3((d.L + 15) / 16), dim3(64), 0, st, d, g, (const double*)R);
+  else
+    hipLaunchKernelGGL((k_ns_out<NT, MODE_OUT, false>), dim3((d.L + 15) / 16), dim3(64), 0, st, d, g, (const double*)R);
+}
+
 // Load, then `steps` Newton-Schulz steps (at least one launch set; steps == 0
 // runs one with coefficients (1, 0, 0), i.e. X_0 itself), the last one in
 // output mode MODE_OUT.
@@ -824,25 +1031,19 @@ void run_ns(const Plan& P, char* ws, RowArgs g, int steps, double a, double b, d
   double* B = (double*)(ws + P.off_b);
   double* scal = (double*)(ws + P.off_scal);
   const dim3 grid(d.nch), blk(kThreads);
-  hipLaunchKernelGGL(k_mx_rows<kLoad>, grid, blk, 0, st, d, g);
   const int n = steps > 0 ? steps : 1;
   if (steps == 0) { a = 1.0; b = 0.0; c = 0.0; }
   const int ne = d.s4 * d.s4;
   if (small_ok(d.s4, n, a)) {
-    // X_n = U R, R from the short-side recurrence: the row pass with a = 0 and
-    // B = R, read from the workspace (scal[0] = 1)
-    hipLaunchKernelGGL(k_mx_reduce, dim3((ne + kThreads - 1) / kThreads), blk, 0, st, ne, d.nch,
-                       (const double*)g.part, A);
-    const int nt = (d.s4 + 15) / 16;
-    auto small = nt <= 1 ? k_mx_small<1> : nt == 2 ? k_mx_small<2> : nt == 3 ? k_mx_small<3> : k_mx_small<4>;
-    hipLaunchKernelGGL(small, dim3(1), dim3(kSmallThreads), 0, st, d.s4, (const double*)A, n, a, b, c, B, scal);
-    Dims d2 = d;
-    d2.fuse_b = 0;
-    RowArgs gi = g;
-    gi.a = 0.0;
-    hipLaunchKernelGGL(k_mx_rows<MODE_OUT>, grid, blk, 0, st, d2, gi);
+    switch ((d.s4 + 15) / 16) {
+      case 1: run_small<1, MODE_OUT>(d, g, A, B, n, a, b, c, st); break;
+      case 2: run_small<2, MODE_OUT>(d, g, A, B, n, a, b, c, st); break;
+      case 3: run_small<3, MODE_OUT>(d, g, A, B, n, a, b, c, st); break;
+      default: run_small<4, MODE_OUT>(d, g, A, B, n, a, b, c, st); break;
+    }
     return;
   }
+  hipLaunchKernelGGL(k_mx_rows<kLoad>, grid, blk, 0, st, d, g);
   for (int i = 0; i < n; ++i) {
     hipLaunchKernelGGL(k_mx_reduce, dim3((ne + kThreads - 1) / kThreads), blk, 0, st, ne, d.nch,
                        (const double*)g.part, A);
