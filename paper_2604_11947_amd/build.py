@@ -1,7 +1,8 @@
 """Compile the HIP library for gfx950, in-tree.
 
-Produces ``libresbm.so`` (bf16 activations) and ``libresbm_f32.so`` (the fp32
-validation build) next to this file.  Run ``python -m paper_2604_11947_amd.build``.
+Produces ``libresbm.so`` (bf16 activations), ``libresbm_f32.so`` (the fp32
+validation build) and ``_marshal.so`` (the binding's argument marshalling, host
+code against torch's and CPython's C++ interfaces) next to this file.  Run ``python -m paper_2604_11947_amd.build``.
 """
 from __future__ import annotations
 
@@ -18,6 +19,8 @@ SRC_TWO = os.path.join(PKG, "csrc", "resbm_two.hip")
 DEPS = [SRC, SRC_MATRIX, SRC_TWO, os.path.join(PKG, "csrc", "resbm_buffer.hpp"), os.path.join(PKG, "csrc", "resbm_host.hpp"), os.path.join(PKG, "csrc", "resbm_mfma.hpp"), os.path.join(PKG, "csrc", "resbm_plan.hpp"),
         os.path.join(PKG, "csrc", "resbm_short.hpp"),
         os.path.join(ROOT, "include", "resbm.h")]
+
+SRC_MARSHAL = os.path.join(PKG, "csrc", "resbm_marshal.cpp")
 
 LIBS = {"bf16": "libresbm.so", "f32": "libresbm_f32.so"}
 
@@ -39,17 +42,31 @@ def command(variant: str, out: str) -> list[str]:
     return cmd
 
 
+def marshal_command(out: str) -> list[str]:
+    import sysconfig
+
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    inc, lib = os.path.join(root, "include"), os.path.join(root, "lib")
+    return [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", inc,
+            "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
+            "-o", out, SRC_MARSHAL, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10", f"-Wl,-rpath,{lib}"]
+
+
 def lib_path(variant: str = "bf16") -> str:
     return os.path.join(PKG, LIBS[variant])
 
 
 def build_all(verbose: bool = False) -> list[str]:
-    """Compile both variants (in parallel); raises on any compiler error."""
+    """Compile both variants and the marshalling module (in parallel); raises on any compiler error."""
     procs = []
-    for variant, name in LIBS.items():
-        out = os.path.join(PKG, name)
+    jobs = [(os.path.join(PKG, name), lambda tmp, v=variant: command(v, tmp)) for variant, name in LIBS.items()]
+    jobs.append((os.path.join(PKG, "_marshal.so"), marshal_command))
+    for out, make in jobs:
         tmp = out + ".tmp"
-        cmd = command(variant, tmp)
+        cmd = make(tmp)
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((out, tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

@@ -14,6 +14,12 @@ import torch
 
 from . import build as _build
 
+try:  # native argument marshalling of the short ops; the Python path below does the same checks
+    from . import _marshal
+    _marshal.init(torch._C._cuda_getCurrentRawStream)
+except (ImportError, AttributeError):
+    _marshal = None
+
 ACT_IDENTITY = 0
 ACT_SILU = 1
 IO_BF16 = 0
@@ -115,6 +121,8 @@ class Library:
             fn = getattr(self.cdll, name)
             fn.restype = res
             fn.argtypes = args
+        # addresses for the marshalling module
+        self._at = {name: ctypes.cast(getattr(self.cdll, name), ctypes.c_void_p).value for name, _, _ in SIGNATURES}
         self.io_code = int(self.cdll.resbm_io_dtype())
         self.io_dtype = torch.bfloat16 if self.io_code == IO_BF16 else torch.float32
 
@@ -146,6 +154,10 @@ class Library:
 
     # ------------------------------------------------------------ ops
     def encode_fwd(self, x_attn, z, W_e, b, a_save=None, act=ACT_SILU, ws=None, stream=None):
+        if _marshal is not None and stream is None:
+            st = _marshal.encode_fwd(self._at["resbm_encode_fwd"], self.io_code, x_attn, z, W_e, b, a_save, act, ws)
+            if st is not None:
+                return self._check("resbm_encode_fwd", st)
         T = z.shape[0]
         n, r = W_e.shape
         io = self.io_dtype
@@ -165,6 +177,10 @@ class Library:
         self._check("resbm_encode_fwd", st)
 
     def decode_fwd(self, b, W_d, z_tilde, add_identity=False, ws=None, stream=None):
+        if _marshal is not None and stream is None:
+            st = _marshal.decode_fwd(self._at["resbm_decode_fwd"], self.io_code, b, W_d, z_tilde, add_identity, ws)
+            if st is not None:
+                return self._check("resbm_decode_fwd", st)
         T = b.shape[0]
         r, n = W_d.shape
         _dtype(b, self.io_dtype, "b")
@@ -179,6 +195,11 @@ class Library:
         self._check("resbm_decode_fwd", st)
 
     def decode_bwd(self, b, W_d, g_zt, g_id, g_b, dW_d, accumulate=False, ws=None, stream=None):
+        if _marshal is not None and stream is None:
+            st = _marshal.decode_bwd(self._at["resbm_decode_bwd"], self.io_code, b, W_d, g_zt, g_id, g_b, dW_d,
+                                     accumulate, ws)
+            if st is not None:
+                return self._check("resbm_decode_bwd", st)
         T = b.shape[0]
         r, n = W_d.shape
         io = self.io_dtype
@@ -201,6 +222,11 @@ class Library:
 
     def encode_bwd(self, z, W_e, a_save, g_b, g_z, dW_e, g_x=None, act=ACT_SILU, accumulate=False, ws=None,
                    stream=None):
+        if _marshal is not None and stream is None:
+            st = _marshal.encode_bwd(self._at["resbm_encode_bwd"], self.io_code, z, W_e, a_save, g_b, g_z, dW_e, g_x,
+                                     act, accumulate, ws)
+            if st is not None:
+                return self._check("resbm_encode_bwd", st)
         T = z.shape[0]
         n, r = W_e.shape
         io = self.io_dtype
@@ -410,6 +436,11 @@ class Library:
 
     def muon_update(self, W, G, M, lr, momentum=0.95, weight_decay=0.0, scale=None, nesterov=False, steps=5,
                     coeffs=NS_QUINTIC, ws=None, stream=None):
+        if _marshal is not None and stream is None:
+            st = _marshal.muon_update(self._at["resbm_muon_update"], W, G, M, lr, momentum, weight_decay,
+                                      -1.0 if scale is None else scale, nesterov, steps, coeffs, ws)
+            if st is not None:
+                return self._check("resbm_muon_update", st)
         p, q = W.shape
         for t, nm in ((W, "W"), (G, "G"), (M, "M")):
             _dtype(t, torch.float32, nm)
