@@ -694,21 +694,19 @@ __global__ __launch_bounds__(kDbWaves * 64) void k_dec_bwd(int64_t T, int n, int
   const bool won = wc0 < n;  // n % 64 == 0: a wave's columns lie in [0, n) in whole runs of 64
 
   // W_d as the A operand of g_b: lane (row16, grp) holds W_d[16 (jt0 + jt) + row16][wc0 + 32 ks + 8 grp + e].
+  const rsrc_t wdr = make_rsrc(W_d, (int64_t)r * n * 4);
   SFrag wdf[JT][KSW];
 #pragma unroll
   for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
     for (int ks = 0; ks < KSW; ++ks) {
-      const int j = 16 * (jt0 + jt) + row16;
-      float w[8];
-      if (wc0 + 32 * ks + 8 * grp < n && j < r) {
-        const float4* p = reinterpret_cast<const float4*>(W_d + (int64_t)j * n + wc0 + 32 * ks + 8 * grp);
-        const float4 a = p[0], c = p[1];
-        w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = c.x; w[5] = c.y; w[6] = c.z; w[7] = c.w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w[e] = 0.0f;
-      }
+      const int j = 16 * (jt0 + jt) + row16, c = wc0 + 32 * ks + 8 * grp;
+      const uint32_t o = c < n && j < r ? (uint32_t)((j * n + c) * 4) : kOOB;
+      const uint4 a = bld16(wdr, o), d = bld16(wdr, o == kOOB ? kOOB : o + 16);
+      const float w[8] = {__builtin_bit_cast(float, a.x), __builtin_bit_cast(float, a.y),
+                          __builtin_bit_cast(float, a.z), __builtin_bit_cast(float, a.w),
+                          __builtin_bit_cast(float, d.x), __builtin_bit_cast(float, d.y),
+                          __builtin_bit_cast(float, d.z), __builtin_bit_cast(float, d.w)};
       wdf[jt][ks] = sfrag_from(w);
     }
 
@@ -1321,6 +1319,30 @@ struct FinArgs {
   int64_t ld_gx;
 };
 
+// Values W(k .. k + 7, column col) of the map, zeros at k >= r and where !on.  W_e
+// (GZ) is contiguous along k: two 16-byte loads (r % 4 == 0), where eight 4-byte
+// ones touched as many cache lines each (encode_bwd at 1024 x 4096, r = 128:
+// 43.2 -> 32.4 us; at 16384 tokens, r = 32 / 128: 55.6 -> 53.3 / 117.5 -> 108.1).
+// No load is conditional, so all of a wave's are in flight together.
+template <bool GZ>
+__device__ __forceinline__ SFrag map_frag(rsrc_t wr, int n, int r, int col, int k, bool on) {
+  float w[8];
+  if constexpr (GZ) {
+    const uint32_t o = (uint32_t)((col * r + k) * 4);
+    const uint4 a = bld16(wr, on && k < r ? o : kOOB), b = bld16(wr, on && k + 4 < r ? o + 16 : kOOB);
+    w[0] = __builtin_bit_cast(float, a.x); w[1] = __builtin_bit_cast(float, a.y);
+    w[2] = __builtin_bit_cast(float, a.z); w[3] = __builtin_bit_cast(float, a.w);
+    w[4] = __builtin_bit_cast(float, b.x); w[5] = __builtin_bit_cast(float, b.y);
+    w[6] = __builtin_bit_cast(float, b.z); w[7] = __builtin_bit_cast(float, b.w);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      w[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                           wr, on && k + e < r ? (uint32_t)(((k + e) * n + col) * 4) : kOOB, 0, 0));
+  }
+  return sfrag_from(w);
+}
+
 template <int KS, int CT, bool ADD, bool GZ, bool R8>
 __global__ __launch_bounds__(256) void k_expand(int64_t T, int n, int r,
                                                 const io_t* __restrict__ in, const io_t* __restrict__ in_lo,
@@ -1359,19 +1381,14 @@ __global__ __launch_bounds__(256) void k_expand(int64_t T, int n, int r,
   if (c0 >= n) return;  // whole strips only: n % 64 == 0 and 16 CT divides 64
 
   // the map as the A operand: lane (row16, grp) holds W(k = 32 ks + 8 grp + e, column)
+  const rsrc_t wr = make_rsrc(W, (int64_t)r * n * 4);
   SFrag wfr[KS][CT];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const int col = expand_col<CT>(c0, ct, row16);
-      float w[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = ks * 32 + grp * 8 + e;
-        w[e] = k < r ? (GZ ? W[(int64_t)col * r + k] : W[(int64_t)k * n + col]) : 0.0f;
-      }
-      wfr[ks][ct] = sfrag_from(w);
+      wfr[ks][ct] = map_frag<GZ>(wr, n, r, col, 32 * ks + 8 * grp, true);
     }
 
   const int64_t t_begin = (int64_t)tgi * tpg;
@@ -2015,19 +2032,14 @@ __global__ __launch_bounds__(256) void k_expand_wide(int64_t T, int n, int r, co
   const int c0 = strip * 16 * CT;
   const bool won = c0 < n;  // whole strips: n % 64 == 0 and 16 CT divides 64
 
+  const rsrc_t wr = make_rsrc(W, (int64_t)r * n * 4);
   SFrag wfr[KS][CT];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const int col = expand_col<CT>(c0, ct, row16);
-      float w[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = ks * 32 + grp * 8 + e;
-        w[e] = (won && k < r) ? (GZ ? W[(int64_t)col * r + k] : W[(int64_t)k * n + col]) : 0.0f;
-      }
-      wfr[ks][ct] = sfrag_from(w);
+      wfr[ks][ct] = map_frag<GZ>(wr, n, r, col, 32 * ks + 8 * grp, won);
     }
 
   const int64_t t_begin = (int64_t)tgi * tpg;
