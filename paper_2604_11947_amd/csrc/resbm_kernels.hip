@@ -314,24 +314,20 @@ __device__ __forceinline__ XFrag tr_frag_wide(const io_t* tile, int row0, int c0
 // ============================================================ encode forward
 // Fragment-ordered hi/lo copy of W_e for the A operand of a = z W_e:
 // fragment f = ks * NT + nt, lane (row16, grp) holds W_e[32 ks + 8 grp + e][16 nt + row16].
-// One wave per block, so that the few fragments spread over many compute units.
+// One wave per block, so that the few fragments spread over many compute units;
+// no division and no conditional load in front of its round trip (encode_fwd at
+// 16384 x 4096, r = 32: 30.0 -> 28.7 us).
 __global__ __launch_bounds__(64) void k_enc_fwd_prep(const float* __restrict__ W_e, int n, int r, int NT,
                                                      void* __restrict__ wf) {
-  const int64_t gid = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  const int64_t total = (int64_t)(n / 32) * NT * 64;
-  if (gid >= total) return;
-  const int l = (int)(gid & 63);
-  const int64_t f = gid >> 6;
-  const int nt = (int)(f % NT);
-  const int ks = (int)(f / NT);
-  const int col = nt * 16 + (l & 15);
-  const int grp = l >> 4;
+  const int l = threadIdx.x, ks = blockIdx.x, nt = blockIdx.y;
+  const int64_t f = (int64_t)ks * NT + nt;
+  const int col = nt * 16 + (l & 15), grp = l >> 4;
+  const rsrc_t we = make_rsrc(W_e, (int64_t)n * r * 4);
   float w[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = ks * 32 + grp * 8 + e;
-    w[e] = col < r ? W_e[(int64_t)k * r + col] : 0.0f;
-  }
+  for (int e = 0; e < 8; ++e)
+    w[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                         we, col < r ? (uint32_t)(((ks * 32 + grp * 8 + e) * r + col) * 4) : kOOB, 0, 0));
   store_sfrag(wf, f, l, w);
 }
 
@@ -1531,21 +1527,14 @@ __global__ __launch_bounds__(256) void k_expand(int64_t T, int n, int r,
 // lane (row16, grp) holds W_d[16 nt + row16][32 ks + 8 grp + e], zeros at rows >= r.
 __global__ __launch_bounds__(64) void k_wd_prep(const float* __restrict__ W_d, int n, int r, int NT,
                                                 void* __restrict__ wf) {
-  const int64_t gid = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  const int64_t total = (int64_t)(n / 32) * NT * 64;
-  if (gid >= total) return;
-  const int l = (int)(gid & 63);
-  const int64_t f = gid >> 6;
-  const int nt = (int)(f % NT), ks = (int)(f / NT);
+  const int l = threadIdx.x, ks = blockIdx.x, nt = blockIdx.y;
+  const int64_t f = (int64_t)ks * NT + nt;
   const int j = nt * 16 + (l & 15), k0 = ks * 32 + (l >> 4) * 8;
-  float w[8];
+  float w[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (j < r) {
     const float4* p = reinterpret_cast<const float4*>(W_d + (int64_t)j * n + k0);
     const float4 a = p[0], c = p[1];
     w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = c.x; w[5] = c.y; w[6] = c.z; w[7] = c.w;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = 0.0f;
   }
   store_sfrag(wf, f, l, w);
 }
@@ -2588,8 +2577,7 @@ int32_t resbm_encode_fwd(int64_t T, int32_t n, int32_t r, int32_t act, const voi
   }
 #endif
   if (!ef_we_lds(p.NT)) {  // fragments for the kernels that read them prepared
-    const int64_t nprep = (int64_t)(n / 32) * p.NT * 64;
-    hipLaunchKernelGGL(k_enc_fwd_prep, dim3((unsigned)ceil_div(nprep, 64)), dim3(64), 0, s, W_e, n, r, p.NT, wf);
+    hipLaunchKernelGGL(k_enc_fwd_prep, dim3(n / 32, p.NT), dim3(64), 0, s, W_e, n, r, p.NT, wf);
   }
   const io_t* X = (const io_t*)x_attn;
   const io_t* Z = (const io_t*)z;
@@ -2682,8 +2670,7 @@ int32_t resbm_decode_bwd(int64_t T, int32_t n, int32_t r, const void* b, const f
 #endif
   if (p.wide) {
     void* wf = w + p.db_wf_off;
-    const int64_t nprep = (int64_t)(n / 32) * p.NT * 64;
-    hipLaunchKernelGGL(k_wd_prep, dim3((unsigned)ceil_div(nprep, 64)), dim3(64), 0, s, W_d, n, r, p.NT, wf);
+    hipLaunchKernelGGL(k_wd_prep, dim3(n / 32, p.NT), dim3(64), 0, s, W_d, n, r, p.NT, wf);
     const bool r8 = expand_r8(r);
 #define CALL(NTV)                                                                                                   \
   do {                                                                                                              \
