@@ -66,6 +66,7 @@ enum Epi : int {
   kEpiAdd = 3,    // C = rne(acc + X) on columns < x_cols, rne(acc) elsewhere
   kEpiPart = 4,   // partial[split] = acc (float32, M x N contiguous per split)
   kEpiBf16Phi = 5,  // C = rne(acc) and D = rne(phi(acc)) (a pre-activation and its activation)
+  kEpiDphiPhi = 7,  // C = rne(acc * phi'(X)) and D = rne(phi(X)) (X as for kEpiDphi)
   kEpiEncode = 6,   // C = rne(acc) (the FFN output z) and D[tile column][row] = C_tile W_e[tile rows]
 };
 
@@ -539,7 +540,7 @@ __device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx
 }
 
 // Stores per lane of one store_pair<EPI>.
-constexpr int pair_stores(int epi) { return epi == kEpiF32 || epi == kEpiPart || epi == kEpiBf16Phi ? 2 : 1; }
+constexpr int pair_stores(int epi) { return epi == kEpiF32 || epi == kEpiPart || epi == kEpiBf16Phi || epi == kEpiDphiPhi ? 2 : 1; }
 
 // Stores two adjacent 16 x 16 tiles: this lane's four columns n .. n + 3 of the
 // first and n + 16 .. n + 19 of the second, row m.  bf16 results: lanes of even
@@ -555,27 +556,36 @@ __device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t 
     store_c4<EPI>(g, rc, rx, rd, split, m, n + 16, v1);
   } else {
     f32x4 v[2] = {v0, v1};
-    if constexpr (EPI == kEpiDphi || EPI == kEpiAdd) {
-#pragma unroll
-      for (int p = 0; p < 2; ++p) {
-        const int c = n + 16 * p;
-        const bool xok = m < g.M && c < (EPI == kEpiDphi ? g.N : g.x_cols);
-        const bf16x4 x = __builtin_bit_cast(bf16x4, bld8(rx, xok ? ((uint32_t)m * (uint32_t)g.ldx + c) * 2 : kOOB));
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if constexpr (EPI == kEpiDphi) v[p][e] *= resbm::silu_grad((float)x[e]);
-          else v[p][e] += (float)x[e];
-        }
-      }
-    }
     const int c8 = n - 4 * (grp & 1) + 16 * (grp & 1);  // n = ... + 4 grp
     const bool ok = m < g.M && c8 < g.N;                // N % 8 == 0: all eight or none
+    // (a's odd rows of 16 lanes, b's even rows) change places; its own inverse
+    auto swap = [](uint32_t& a, uint32_t& b) {
+      const auto x = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+      a = x[0];
+      b = x[1];
+    };
+    if constexpr (EPI == kEpiDphi || EPI == kEpiDphiPhi || EPI == kEpiAdd) {
+      const bool xok = m < g.M && c8 < (EPI == kEpiAdd ? g.x_cols : g.N);
+      uint4 u = bld16(rx, xok ? ((uint32_t)m * (uint32_t)g.ldx + c8) * 2 : kOOB);
+      if constexpr (EPI == kEpiDphiPhi)
+        bst16(rd, ok ? ((uint32_t)m * (uint32_t)g.ldd + c8) * 2 : kOOB, silu8(u));
+      swap(u.x, u.z);
+      swap(u.y, u.w);
+      const bf16x4 x[2] = {__builtin_bit_cast(bf16x4, make_uint2(u.x, u.y)),
+                           __builtin_bit_cast(bf16x4, make_uint2(u.z, u.w))};
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (EPI == kEpiAdd) v[p][e] += (float)x[p][e];
+          else v[p][e] *= resbm::silu_grad((float)x[p][e]);
+        }
+    }
     auto put = [&](rsrc_t r, int64_t ld, bf16x4 h0, bf16x4 h1) {
-      const uint2 a = __builtin_bit_cast(uint2, h0), b = __builtin_bit_cast(uint2, h1);
-      // (a's odd rows of 16 lanes, b's even rows) change places
-      const auto x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
-      const auto y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
-      bst16(r, ok ? ((uint32_t)m * (uint32_t)ld + c8) * 2 : kOOB, make_uint4(x[0], y[0], x[1], y[1]));
+      uint2 a = __builtin_bit_cast(uint2, h0), b = __builtin_bit_cast(uint2, h1);
+      swap(a.x, b.x);
+      swap(a.y, b.y);
+      bst16(r, ok ? ((uint32_t)m * (uint32_t)ld + c8) * 2 : kOOB, make_uint4(a.x, a.y, b.x, b.y));
     };
     bf16x4 h[2];
 #pragma unroll
@@ -1306,13 +1316,6 @@ __global__ __launch_bounds__(256) void k_splitk_sum(const float* __restrict__ pa
   reinterpret_cast<float4*>(out)[q] = a;
 }
 
-// p[i] = rne(silu(v[i])), 8 elements per thread (count % 8 == 0).
-__global__ __launch_bounds__(256) void k_silu(const __bf16* __restrict__ v, int64_t count, __bf16* __restrict__ p) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q * 8 >= count) return;
-  reinterpret_cast<uint4*>(p)[q] = silu8(reinterpret_cast<const uint4*>(v)[q]);
-}
-
 // a = sum over the NT column tiles, in order, of the encoder partials;
 // b = rne(x_attn[:, :r] + phi(a)); a_save = a.  4 columns per thread.
 __global__ __launch_bounds__(256) void k_enc_finish(int64_t T, int r, int NT, int act, const float* __restrict__ part,
@@ -1645,17 +1648,14 @@ int32_t resbm2_decode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   // g_v = (g_zt W4^T) * phi'(v)   (B(k, j) = W4[j][k]: K-contiguous)
   GemmArgs g = args(Ti, m, n, g_zt, ld_gzt, bg, W4, n, bw4, g_v, m, bv);
   if (silu) {
+    // and phi(v), from the v that the epilogue reads (16384 x 1024: a launch of 10.8 us)
     g.X = v; g.ldx = m; g.x_bytes = (int64_t)bv;
-    gemm<true, true, kEpiDphi, false>(rows_for(Ti, m), g, 1, st);
+    g.D = pv; g.ldd = m; g.d_bytes = (int64_t)bv;
+    gemm<true, true, kEpiDphiPhi, false>(rows_for(Ti, m), g, 1, st);
   } else {
     gemm<true, true, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
   }
-  // dW4 = phi(v)^T g_zt   (A(i, k) = phi(v)[k][i], B(k, j) = g_zt[k][j]); phi(v) formed once
-  if (silu) {
-    const int64_t cnt = T * m;
-    hipLaunchKernelGGL(k_silu, dim3((unsigned)((cnt / 8 + 255) / 256)), dim3(256), 0, st, (const __bf16*)v, cnt,
-                       (__bf16*)pv);
-  }
+  // dW4 = phi(v)^T g_zt   (A(i, k) = phi(v)[k][i], B(k, j) = g_zt[k][j])
   g = args(m, n, Ti, silu ? pv : v, m, bv, g_zt, ld_gzt, bg, nullptr, 0, 0);
   weight_grad<false>(wide_for(m, n), g, p.dW4, dW4, part, st);
   // dW3 = b^T g_v
