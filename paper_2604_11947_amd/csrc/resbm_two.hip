@@ -1103,20 +1103,24 @@ __global__ __launch_bounds__(512) void k_qkv_prep(DqArgs g) {
   }
 }
 
-// Columns [16 CT blockIdx.x, ...) of out for g.rows tokens.  The 8 waves take
+// Columns [16 CT blockIdx.x, ...) of out for g.rows tokens.  The NW waves take
 // the 64-row units of W_qkv in turn: a unit goes through the wave's own LDS
 // tile and is read back transposed, W_d gamma (hi and lo: two products) comes
 // from the cache in fragment order (or, behind the units that the workspace
-// holds, is split here); the next two units' loads are in flight meanwhile.  The waves' parts of M meet in LDS in wave order and are kept
-// there as hi and lo planes; then the waves take 32-row tiles of out in turn.
-// Against the 256 x 256 tiles that rebuilt z~ gamma per stage: 158 -> 37.5 us at
-// 1024 x 4096 x 6144, r = 32, and 973 -> 94 at 16384 rows.  What bounds it: the
-// latency of W_qkv's 64-row units (8 per wave) at few rows, the writes of out at many.
+// holds, is split here); the next units' loads are in flight meanwhile (two with
+// eight waves, one with sixteen, whose registers hold no more).  The waves' parts
+// of M meet in LDS in wave order and are kept there as hi and lo planes; then the
+// waves take 32-row tiles of out in turn.
+// Against the 256 x 256 tiles that rebuilt z~ gamma per stage: 158 -> 36.4 us at
+// 1024 x 4096 x 6144, r = 32 (37.3 with eight waves instead of sixteen), and
+// 973 -> 94 at 16384 rows.  What bounds it: the latency of W_qkv's 64-row units
+// at few rows, the writes of out at many.
 // (Splitting W_d gamma in every block instead of reading fragments: 43.8 us.)
-template <int KS, int CT>
-__global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
+template <int KS, int CT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   constexpr int KP = 32 * KS, JT = 2 * KS, WC = 16 * CT, LPR = WC / 8, RPI = 64 / LPR, NQ = 64 / RPI;
-  constexpr int STAGE = 8 * 64 * WC * 2, PP = KP + 4, PART = 8 * WC * PP * 4;
+  constexpr int STAGE = NW * 64 * WC * 2, PP = KP + 4, PART = NW * WC * PP * 4;
+  constexpr int AHEAD = NW == 8 ? 2 : 1;  // units of W_qkv in flight per wave
   __shared__ __attribute__((aligned(16))) char smem[STAGE > PART ? STAGE : PART];
   __shared__ __attribute__((aligned(16))) __bf16 s_m[2][WC * KP];
   __shared__ float s_sc[kScRows];
@@ -1132,7 +1136,7 @@ __global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
   const int tb = blockIdx.y * g.rows, te = min(g.T, tb + g.rows);
   const float inv_n = 1.0f / (float)g.n;
   auto row_scales = [&](int ts) {
-    for (int i = threadIdx.x; i < kScRows && ts + i < te; i += 512) {
+    for (int i = threadIdx.x; i < kScRows && ts + i < te; i += 64 * NW) {
       float q = 0.0f;
       for (int k = 0; k < g.ncg; ++k) q += g.ssq[(int64_t)k * g.T + ts + i];
       s_sc[i] = 1.0f / sqrtf(q * inv_n + g.eps);
@@ -1180,8 +1184,8 @@ __global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
           d[ks][jt] = wd_gamma(g, 16 * jt + row16, 64 * u + 32 * ks + 8 * grp);
         }
       }
-    load_d(u + 8);
-    load_w(wq, u + 16);
+    load_d(u + NW);
+    load_w(wq, u + AHEAD * NW);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wave's own tile is complete
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
@@ -1198,11 +1202,13 @@ __global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
   };
   load_w(wa, wave);
   load_d(wave);
-  load_w(wb, wave + 8);
+  if constexpr (AHEAD == 2) load_w(wb, wave + NW);
   row_scales(tb);  // (read behind the barriers below)
-  for (int u = wave; u < nu; u += 16) {
+  for (int u = wave; u < nu; u += AHEAD * NW) {
     unit(wa, u);
-    if (u + 8 < nu) unit(wb, u + 8);
+    if constexpr (AHEAD == 2) {
+      if (u + NW < nu) unit(wb, u + NW);
+    }
   }
   __syncthreads();  // the parts overlap the tiles
   // lane (row16, grp): part of M[16 jt + 4 grp + v][c0 + 16 ct + row16]
@@ -1214,11 +1220,11 @@ __global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
       *reinterpret_cast<float4*>(part + (wave * WC + 16 * ct + row16) * PP + 16 * jt + 4 * grp) =
           make_float4(acc[jt][ct][0], acc[jt][ct][1], acc[jt][ct][2], acc[jt][ct][3]);
   __syncthreads();
-  for (int idx = threadIdx.x; idx < WC * KP / 4; idx += 512) {
+  for (int idx = threadIdx.x; idx < WC * KP / 4; idx += 64 * NW) {
     const int c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
     float m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float4 p = *reinterpret_cast<const float4*>(part + (w * WC + c) * PP + j);
       m[0] += p.x; m[1] += p.y; m[2] += p.z; m[3] += p.w;
     }
@@ -1267,13 +1273,13 @@ __global__ __launch_bounds__(512) void k_qkv_strip(DqArgs g) {
     }
     const int tl = min(te, ts + kScRows);
     load_b(ts + 32 * wave + row16);
-    for (int t0 = ts + 32 * wave; t0 < tl; t0 += 256) {
+    for (int t0 = ts + 32 * wave; t0 < tl; t0 += 32 * NW) {
       bf16x8 bv[2][KS];
 #pragma unroll
       for (int p = 0; p < 2; ++p)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bv[p][ks] = bn[p][ks];
-      load_b(t0 + 256 + row16);
+      load_b(t0 + 32 * NW + row16);
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
         const int t = t0 + 16 * p + row16;
@@ -1506,8 +1512,9 @@ template <int KS>
 void launch_qkv(const DqArgs& g, int ct, int ranges, hipStream_t st) {
   hipLaunchKernelGGL(k_qkv_prep<KS>, dim3((g.T + 63) / 64, g.ncg + 1), dim3(512), 0, st, g);
   const dim3 grid((g.N + 16 * ct - 1) / (16 * ct), ranges);
-  if (ct == 2) hipLaunchKernelGGL((k_qkv_strip<KS, 2>), grid, dim3(512), 0, st, g);
-  else hipLaunchKernelGGL((k_qkv_strip<KS, 4>), grid, dim3(512), 0, st, g);
+  constexpr int NW = KS == 1 ? 16 : 8;
+  if (ct == 2) hipLaunchKernelGGL((k_qkv_strip<KS, 2, NW>), grid, dim3(64 * NW), 0, st, g);
+  else hipLaunchKernelGGL((k_qkv_strip<KS, 4, 8>), grid, dim3(512), 0, st, g);
 }
 
 int32_t check_ws(size_t need, const void* ws, size_t ws_bytes) {
