@@ -355,8 +355,8 @@ int32_t resbm_ffn_encode_fwd(int64_t T, int32_t d_ff, int32_t n, int32_t r, int3
  *     RMSNorm(x)[t][c] = x[t][c] / sqrt(mean_c' x[t][c']^2 + eps) gamma[c].
  * Neither z~ nor its normalised rows are written: the row scale and gamma are
  * linear factors, so out[t] = s_t b[t] (W_d diag(gamma) W_qkv), with the r x N
- * matrix formed in the call (W_d gamma and it as hi + lo bf16 parts, float32
- * sums) and s_t = 1 / sqrt(mean z~[t]^2 + eps) from the float32 z~.  An infinite
+ * matrix formed in the call (W_d gamma as hi + lo bf16 parts, float32 sums, all
+ * of whose bits the sum over r uses) and s_t = 1 / sqrt(mean z~[t]^2 + eps) from the float32 z~.  An infinite
  * gamma or W_qkv entry may give NaN where the sum over c would give an infinity.
  * A caller that also needs z~ (its residual stream)
  * still runs resbm_decode_fwd.

@@ -1109,8 +1109,12 @@ __global__ __launch_bounds__(512) void k_qkv_prep(DqArgs g) {
 // from the cache in fragment order (or, behind the units that the workspace
 // holds, is split here); the next units' loads are in flight meanwhile (two with
 // eight waves, one with sixteen, whose registers hold no more).  The waves' parts
-// of M meet in LDS in wave order and are kept there as hi and lo planes; then the
-// waves take 32-row tiles of out in turn.
+// of M meet in LDS in wave order and are kept there as three bf16 planes, which
+// hold all 24 bits of the float32 sums: the sum over r that follows may cancel
+// (rows of W_d that share a component, a payload orthogonal to it), and with two
+// planes the error was then up to 1.4 times that of z~ formed first in float32
+// (1.9e-2 against 1.4e-2 of the result where the component is 1000 times the
+// differences; three planes 1.4e-2).  Then the waves take 32-row tiles of out in turn.
 // Against the 256 x 256 tiles that rebuilt z~ gamma per stage: 158 -> 36.4 us at
 // 1024 x 4096 x 6144, r = 32 (37.3 with eight waves instead of sixteen), and
 // 973 -> 94 at 16384 rows.  What bounds it: the latency of W_qkv's 64-row units
@@ -1122,7 +1126,7 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   constexpr int STAGE = NW * 64 * WC * 2, PP = KP + 4, PART = NW * WC * PP * 4;
   constexpr int AHEAD = NW == 8 ? 2 : 1;  // units of W_qkv in flight per wave
   __shared__ __attribute__((aligned(16))) char smem[STAGE > PART ? STAGE : PART];
-  __shared__ __attribute__((aligned(16))) __bf16 s_m[2][WC * KP];
+  static_assert(3 * WC * KP * 2 <= PART, "the planes of M take the parts' place");
   __shared__ float s_sc[kScRows];
   const int lane = threadIdx.x & 63, row16 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1220,38 +1224,54 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
       *reinterpret_cast<float4*>(part + (wave * WC + 16 * ct + row16) * PP + 16 * jt + 4 * grp) =
           make_float4(acc[jt][ct][0], acc[jt][ct][1], acc[jt][ct][2], acc[jt][ct][3]);
   __syncthreads();
-  for (int idx = threadIdx.x; idx < WC * KP / 4; idx += 64 * NW) {
-    const int c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
-    float m[4] = {0.f, 0.f, 0.f, 0.f};
+  constexpr int NI = (WC * KP / 4 + 64 * NW - 1) / (64 * NW);
+  float m4[NI][4];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float4 p = *reinterpret_cast<const float4*>(part + (w * WC + c) * PP + j);
-      m[0] += p.x; m[1] += p.y; m[2] += p.z; m[3] += p.w;
-    }
-    bf16x4 h, l;
+  for (int i = 0; i < NI; ++i) {
+    const int idx = threadIdx.x + i * 64 * NW, c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
+    m4[i][0] = m4[i][1] = m4[i][2] = m4[i][3] = 0.0f;
+    if (idx < WC * KP / 4) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      __bf16 a, b;
-      resbm::split_hi_lo(m[e], a, b);
-      h[e] = a;
-      l[e] = b;
+      for (int w = 0; w < NW; ++w) {
+        const float4 p = *reinterpret_cast<const float4*>(part + (w * WC + c) * PP + j);
+        m4[i][0] += p.x; m4[i][1] += p.y; m4[i][2] += p.z; m4[i][3] += p.w;
+      }
     }
-    const int pos = c * KP + resbm::tile_col<KP>(c, j);
-    *reinterpret_cast<uint2*>(&s_m[0][pos]) = __builtin_bit_cast(uint2, h);
-    *reinterpret_cast<uint2*>(&s_m[1][pos]) = __builtin_bit_cast(uint2, l);
+  }
+  __syncthreads();  // the planes overlap the parts
+  __bf16* const planes = reinterpret_cast<__bf16*>(smem);
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int idx = threadIdx.x + i * 64 * NW, c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
+    if (idx < WC * KP / 4) {
+      bf16x4 p[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const __bf16 h = (__bf16)m4[i][e];
+        const float rest = m4[i][e] - (float)h;  // exact
+        const __bf16 q = (__bf16)rest;
+        p[0][e] = h;
+        p[1][e] = q;
+        p[2][e] = (__bf16)(rest - (float)q);
+      }
+      const int pos = c * KP + resbm::tile_col<KP>(c, j);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(planes + k * WC * KP + pos) = __builtin_bit_cast(uint2, p[k]);
+    }
   }
   __syncthreads();
 
   // M as the first operand: row i of tile ct is column expand_col(ct, i), so that
   // a lane ends up with runs of 8 consecutive columns
-  resbm::SFragB m[CT][KS];
+  bf16x8 m[CT][KS][3];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const int c = resbm::expand_col<CT>(0, ct, row16), pos = c * KP + resbm::tile_col<KP>(c, 32 * ks + 8 * grp);
-      m[ct][ks].hi = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&s_m[0][pos]));
-      m[ct][ks].lo = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&s_m[1][pos]));
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        m[ct][ks][k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(planes + k * WC * KP + pos));
     }
   const rsrc_t rb = make_rsrc(g.b, (int64_t)g.T * g.r * 2), ro = make_rsrc(g.out, g.out_bytes);
   bf16x8 bn[2][KS];
@@ -1289,10 +1309,10 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
         for (int ct = 0; ct < CT; ++ct) {
           o[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m[ct][ks].lo, bv[p][ks], o[ct], 0, 0, 0);
-            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m[ct][ks].hi, bv[p][ks], o[ct], 0, 0, 0);
-          }
+          for (int k = 2; k >= 0; --k)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+              o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m[ct][ks][k], bv[p][ks], o[ct], 0, 0, 0);
         }
 #pragma unroll
         for (int h = 0; h < CT / 2; ++h) {
