@@ -1103,6 +1103,78 @@ __global__ __launch_bounds__(512) void k_qkv_prep(DqArgs g) {
   }
 }
 
+// The columns [c0, c0 + 16 CT) of out for the rows [tb, te) as sums over n of
+// z~ gamma (rounded to bf16) times W_qkv: the strips whose part of M is not finite.
+// There the order matters.  M[j][c] is an infinity or NaN for every j where one
+// weight of the column is infinite, and its sum over j NaN, where the sum over n has
+// one infinite term with a sign of its own.  No tiles and no LDS: weights like these
+// are an error to be seen in the output, not a load to be fast for.
+template <int KS, int CT, int NW>
+__device__ __forceinline__ void qkv_direct(const DqArgs& g, int c0, int tb, int te) {
+  const int lane = threadIdx.x & 63, row16 = lane & 15, grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const rsrc_t rb = make_rsrc(g.b, (int64_t)g.T * g.r * 2), ro = make_rsrc(g.out, g.out_bytes);
+  const float inv_n = 1.0f / (float)g.n;
+  for (int t0 = tb + 16 * wave; t0 < te; t0 += 16 * NW) {
+    const int t = t0 + row16;
+    bf16x8 bv[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int j = 32 * ks + 8 * grp;
+      bv[ks] = __builtin_bit_cast(bf16x8, bld16(rb, t < te && j < g.r ? (uint32_t)(((int64_t)t * g.r + j) * 2) : kOOB));
+    }
+    f32x4 o[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) o[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < g.n; c += 32) {
+      bf16x8 zg;  // z~[t] gamma at columns c + 16 (e / 4) + 4 grp + e % 4
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          resbm::SFragB w;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int j = 32 * ks + 8 * grp + e;
+            __bf16 hi, lo;
+            resbm::split_hi_lo(j < g.r ? g.W_d[(int64_t)j * g.n + c + 16 * h + row16] : 0.0f, hi, lo);
+            w.hi[e] = hi;
+            w.lo[e] = lo;
+          }
+          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.lo, bv[ks], z, 0, 0, 0);
+          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.hi, bv[ks], z, 0, 0, 0);
+        }
+        const float4 gm = *reinterpret_cast<const float4*>(g.gamma + c + 16 * h + 4 * grp);
+        zg[4 * h] = (__bf16)(z[0] * gm.x);
+        zg[4 * h + 1] = (__bf16)(z[1] * gm.y);
+        zg[4 * h + 2] = (__bf16)(z[2] * gm.z);
+        zg[4 * h + 3] = (__bf16)(z[3] * gm.w);
+      }
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int col = c0 + 16 * ct + row16;
+        bf16x8 w;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          w[e] = col < g.N ? g.W[(int64_t)(c + 16 * (e >> 2) + 4 * grp + (e & 3)) * g.N + col] : (__bf16)0.0f;
+        o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, zg, o[ct], 0, 0, 0);
+      }
+    }
+    float q = 0.0f;
+    for (int k = 0; k < g.ncg; ++k) q += t < te ? g.ssq[(int64_t)k * g.T + t] : 0.0f;
+    const float sc = 1.0f / sqrtf(q * inv_n + g.eps);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {  // lane (row16, grp): out[t][c0 + 16 ct + 4 grp + v]
+      const int col = c0 + 16 * ct + 4 * grp;
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[ct][e] * sc);
+      bst8(ro, t < te && col < g.N ? (uint32_t)(((int64_t)t * g.ld_out + col) * 2) : kOOB, __builtin_bit_cast(uint2, v));
+    }
+  }
+}
+
 // Columns [16 CT blockIdx.x, ...) of out for g.rows tokens.  The NW waves take
 // the 64-row units of W_qkv in turn: a unit goes through the wave's own LDS
 // tile and is read back transposed, W_d gamma (hi and lo: two products) comes
@@ -1226,6 +1298,7 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   __syncthreads();
   constexpr int NI = (WC * KP / 4 + 64 * NW - 1) / (64 * NW);
   float m4[NI][4];
+  int odd = 0;  // an infinity or NaN among this thread's sums
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int idx = threadIdx.x + i * 64 * NW, c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
@@ -1237,8 +1310,13 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
         m4[i][0] += p.x; m4[i][1] += p.y; m4[i][2] += p.z; m4[i][3] += p.w;
       }
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) odd |= !isfinite(m4[i][e]);
   }
-  __syncthreads();  // the planes overlap the parts
+  if (__syncthreads_or(odd)) {  // (a barrier: the planes overlap the parts)
+    qkv_direct<KS, CT, NW>(g, c0, tb, te);
+    return;
+  }
   __bf16* const planes = reinterpret_cast<__bf16*>(smem);
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
