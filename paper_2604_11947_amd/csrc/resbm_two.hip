@@ -1180,7 +1180,9 @@ __device__ __forceinline__ void qkv_direct(const DqArgs& g, int c0, int tb, int 
 // tile and is read back transposed, W_d gamma (hi and lo: two products) comes
 // from the cache in fragment order (or, behind the units that the workspace
 // holds, is split here); the next units' loads are in flight meanwhile (two with
-// eight waves, one with sixteen, whose registers hold no more).  The waves' parts
+// eight waves; one with sixteen, and in 64-column strips at r > 32, whose registers
+// hold no more: two spilled 93 there, one 16, 192 -> 163 us at 16384 x 4096 x 6144,
+// r = 64).  The waves' parts
 // of M meet in LDS in wave order and are kept there as three bf16 planes, which
 // hold all 24 bits of the float32 sums: the sum over r that follows may cancel
 // (rows of W_d that share a component, a payload orthogonal to it), and with two
@@ -1196,7 +1198,8 @@ template <int KS, int CT, int NW>
 __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   constexpr int KP = 32 * KS, JT = 2 * KS, WC = 16 * CT, LPR = WC / 8, RPI = 64 / LPR, NQ = 64 / RPI;
   constexpr int STAGE = NW * 64 * WC * 2, PP = KP + 4, PART = NW * WC * PP * 4;
-  constexpr int AHEAD = NW == 8 ? 2 : 1;  // units of W_qkv in flight per wave
+  // units of W_qkv in flight per wave
+  constexpr int AHEAD = NW == 8 && KS * CT < 8 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) char smem[STAGE > PART ? STAGE : PART];
   static_assert(3 * WC * KP * 2 <= PART, "the planes of M take the parts' place");
   __shared__ float s_sc[kScRows];
@@ -1960,7 +1963,9 @@ int32_t resbm_decode_qkv_fwd(int64_t T, int32_t n, int32_t r, int32_t N, const v
     // 32-column strips while out is short (more blocks: 37.5 us either way at
     // 1024 x 4096 x 6144, r = 32; 27.6 against 52.4 at 300 x 2112 x 4000, r = 64);
     // beyond, 64-column ones write whole 128-byte lines (16384 x 4096 x 6144:
-    // 94 against 113 us; at r = 64 their spills cost more up to 8192 rows)
+    // 94 against 113 us).  Above r = 32 they win later, the narrower out is the
+    // later (r = 64: 85 and 83 us at 4096 x 4096 x 6144, 137 against 118 at 8192 rows;
+    // r = 48: 50 against 55 at 6000 x 2048 x 4000)
     const int ct = g.T <= (KS == 1 ? 2048 : 8192) ? 2 : 4, strips = (N + 16 * ct - 1) / (16 * ct);
     // token ranges: blocks for the whole chip, one per compute unit (two: 74 against 44 us at 1024 rows)
     int ranges = std::max(1, std::min(kNumBlocks / strips, (g.T + 255) / 256));
