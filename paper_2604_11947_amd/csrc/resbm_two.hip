@@ -193,6 +193,30 @@ struct Operand {
   }
 };
 
+// Direct-to-LDS staging of a k-major [64][I] operand tile (buffer loads with the
+// LDS destination): wave w of NW moves the 1 KiB blocks p NW + w of the tile, lane l
+// filling bytes [16 l, 16 l + 16) of its block, so each lane fetches the chunk
+// whose swizzled position that is (tr_col's XOR, its own inverse).  Chunks outside
+// [0, NI) x [0, kend) are fetched at kOOB and land as zeros.
+template <int I, int NW>
+__device__ __forceinline__ void dma_tile(rsrc_t src, int64_t ld, int i0, int NI, int k0, int kend, __bf16* tile,
+                                         int wave, int lane) {
+  static_assert(I % 128 == 0, "direct staging of a k-major tile needs rows of a multiple of 128");
+  constexpr int BLOCKS = I * KT * 2 / 1024;
+  static_assert(BLOCKS % NW == 0, "tile blocks must divide over the waves");
+#pragma unroll
+  for (int p = 0; p < BLOCKS / NW; ++p) {
+    const int blk = p * NW + wave;
+    const int o = blk * 1024 + lane * 16;
+    const int row = o / (I * 2), pc = (o >> 4) % (I / 8);
+    const int f = ((row & 3) | ((row >> 1) & 4)) << 1;  // tr_col's XOR
+    const int k = k0 + row, idx = i0 + 8 * (((pc ^ f) & 15) | (pc & ~15));
+    const bool ok = idx < NI && k < kend;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)(tile + blk * 512), 16,
+                                             ok ? (uint32_t)(((int64_t)k * ld + idx) * 2) : kOOB, 0, 0, 0);
+  }
+}
+
 // Block index -> tile index.  Consecutive blocks are dispatched to the eight
 // XCDs in turn; each XCD is given a contiguous range of tiles, and tile indices
 // run along N first, so the tiles resident on one XCD share the rows of A (the
@@ -1409,6 +1433,163 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   }
 }
 
+// The other order, for many tokens and a narrow n (see qkv_by_tiles): out on 256 x 256
+// tiles (8 waves of 128 x 64, 64-deep stages, double buffered).  The A operand of every stage -- 64 columns
+// of z~ for the tile's 256 rows -- is rebuilt in the block instead of read:
+// wave w forms rows [32 w, 32 w + 32) of it as b W_d (W_d hi and lo: two
+// products per 16 x 16 piece and 32-deep k-step of r), multiplies by gamma and
+// rounds to bf16 into the LDS tile; W_qkv streams straight into LDS.  Each wave
+// also sums the squares of its rows' float32 z~ over the whole K loop; the row
+// scale 1 / sqrt(mean z~^2 + eps) is applied in the epilogue (RMSNorm is a
+// per-row scale of z~ gamma).  The rebuild costs 2 KS / 4 of the tile's
+// products (W_d as hi + lo, KS = r / 32 rounded up).
+template <int KS>
+__global__ __launch_bounds__(512) void k_dec_qkv(DqArgs g) {
+  constexpr int BM = 256, BN = 256, WM = 2, WN = 4, NW = 8;
+  constexpr int FM = BM / (16 * WM), FN = BN / (16 * WN);
+  __shared__ __attribute__((aligned(16))) __bf16 s_a0[BM * KT], s_a1[BM * KT];
+  __shared__ __attribute__((aligned(16))) __bf16 s_b0[BN * KT], s_b1[BN * KT];
+  __shared__ float s_ssq[BM];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row16 = lane & 15, grp = lane >> 4;
+  const int wm = wave % WM, wn = wave / WM;
+  const int tiles_n = (g.N + BN - 1) / BN;
+  const int t = xcd_tile(blockIdx.x, gridDim.x);
+  const int m0 = (t / tiles_n) * BM, n0 = (t % tiles_n) * BN;
+  const int nst = g.n / KT;
+  const int nc = g.n / 16;
+
+  const rsrc_t rw = make_rsrc(g.W, g.w_bytes);
+  const rsrc_t rbr = make_rsrc(g.b + (int64_t)m0 * g.r, (int64_t)max(0, min(BM, g.T - m0)) * g.r * 2);
+  const rsrc_t rwd = make_rsrc(g.wf, (int64_t)KS * nc * 2048);
+  const rsrc_t rg = make_rsrc(g.gamma, (int64_t)g.n * 4);
+
+  // b rows of this wave's rebuild (the A slot: lane holds b[row][32 ks + 8 grp + e])
+  bf16x8 bfr[2][KS];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int row = 32 * wave + 16 * rb + row16, j = 32 * ks + 8 * grp;
+      bfr[rb][ks] = __builtin_bit_cast(bf16x8, bld16(rbr, j < g.r ? (uint32_t)((row * g.r + j) * 2) : kOOB));
+    }
+  // W_d fragments and gamma of a stage, loaded one stage ahead
+  struct Wd {
+    bf16x8 hi[4][KS], lo[4][KS];
+    float4 gm[4];
+  };
+  auto load_wd = [&](Wd& w, int s) {
+    const bool ok = s < nst;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+      const int c16 = (s * KT) / 16 + cb;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int64_t f = (int64_t)ks * nc + c16;
+        w.hi[cb][ks] = __builtin_bit_cast(bf16x8, bld16(rwd, ok ? (uint32_t)(((2 * f) * 64 + lane) * 16) : kOOB));
+        w.lo[cb][ks] = __builtin_bit_cast(bf16x8, bld16(rwd, ok ? (uint32_t)(((2 * f + 1) * 64 + lane) * 16) : kOOB));
+      }
+      const uint4 gv = bld16(rg, ok ? (uint32_t)((s * KT + 16 * cb + 4 * grp) * 4) : kOOB);
+      w.gm[cb] = make_float4(__builtin_bit_cast(float, gv.x), __builtin_bit_cast(float, gv.y),
+                             __builtin_bit_cast(float, gv.z), __builtin_bit_cast(float, gv.w));
+    }
+  };
+  float ssq[2] = {0.f, 0.f};
+  // z~ gamma for the stage's 64 columns and the wave's 32 rows, into the A tile
+  auto rebuild = [&](const Wd& w, __bf16* a) {
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.hi[cb][ks], bfr[rb][ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.lo[cb][ks], bfr[rb][ks], acc, 0, 0, 0);
+        }
+        // lane (row16, grp): z~[row][16 cb + 4 grp + v]
+        const float gv[4] = {w.gm[cb].x, w.gm[cb].y, w.gm[cb].z, w.gm[cb].w};
+        bf16x4 h;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          ssq[rb] = fmaf(acc[v], acc[v], ssq[rb]);
+          h[v] = (__bf16)(acc[v] * gv[v]);
+        }
+        const int row = 32 * wave + 16 * rb + row16;
+        *reinterpret_cast<uint2*>(a + tile_pos<true, BM>(row, 16 * cb + 4 * grp)) = __builtin_bit_cast(uint2, h);
+      }
+  };
+
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto products_kk = [&](const __bf16* ta, const __bf16* tb, int kk) {
+    bf16x8 fa[FM], fb[FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[i] = frag<true, BM>(ta, (wm * FM + i) * 16, kk, row16, grp);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[j] = frag<false, BN>(tb, (wn * FN + j) * 16, kk, row16, grp);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+  };
+
+  Wd wd;
+  load_wd(wd, 0);
+  // stage 0: its A tile and the B tile
+  rebuild(wd, s_a0);
+  load_wd(wd, 1);
+  dma_tile<BN, NW>(rw, g.N, n0, g.N, 0, g.n, s_b0, wave, lane);
+  auto step = [&](int s, const __bf16* a, const __bf16* b, __bf16* na, __bf16* nb) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (s + 1 < nst) {
+      dma_tile<BN, NW>(rw, g.N, n0, g.N, (s + 1) * KT, g.n, nb, wave, lane);
+      rebuild(wd, na);
+      load_wd(wd, s + 2);
+    }
+    products_kk(a, b, 0);
+    products_kk(a, b, 1);
+  };
+  for (int s = 0; s < nst; s += 2) {
+    step(s, s_a0, s_b0, s_a1, s_b1);
+    if (s + 1 < nst) step(s + 1, s_a1, s_b1, s_a0, s_b0);
+  }
+
+  // row sums of squares: the four lane groups of a row, then one writer per row
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    float v = ssq[rb];
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (grp == 0) s_ssq[32 * wave + 16 * rb + row16] = v;
+  }
+  __syncthreads();
+
+  const rsrc_t ro = make_rsrc(g.out, g.out_bytes);
+  const float inv_n = 1.0f / (float)g.n;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int ml = (wm * FM + i) * 16 + row16;
+    const int m = m0 + ml;
+    const float sc = 1.0f / sqrtf(s_ssq[ml] * inv_n + g.eps);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int n = n0 + (wn * FN + j) * 16 + 4 * grp;
+      const bool ok = m < g.T && n < g.N;
+      bf16x4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (__bf16)(acc[i][j][e] * sc);
+      bst8(ro, ok ? (uint32_t)(((int64_t)m * g.ld_out + n) * 2) : kOOB, __builtin_bit_cast(uint2, h));
+    }
+  }
+}
+
 // out[i] = sum over s in order of part[s][i], i < count (count % 4 == 0).
 __global__ __launch_bounds__(256) void k_splitk_sum(const float* __restrict__ part, int S, int64_t count,
                                                     float* __restrict__ out) {
@@ -1607,6 +1788,34 @@ void weight_grad(Shape s, GemmArgs g, const Split& sp, float* W, void* part, hip
   const int64_t count = (int64_t)g.M * g.N;
   hipLaunchKernelGGL(k_splitk_sum, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, st, (const float*)part,
                      sp.S, count, W);
+}
+
+// 16-column tiles per strip of decode_qkv_fwd.  32-column strips while out is short
+// (more blocks: 37.5 us either way at 1024 x 4096 x 6144, r = 32; 27.6 against 52.4 at
+// 300 x 2112 x 4000, r = 64); beyond, 64-column ones write whole 128-byte lines
+// (16384 x 4096 x 6144: 94 against 113 us).  Above r = 32 they win later, the narrower
+// out is the later (r = 64: 85 and 83 us at 4096 x 4096 x 6144, 137 against 118 at 8192
+// rows; r = 48: 50 against 55 at 6000 x 2048 x 4000).
+int qkv_ct(int64_t T, int KS) { return T <= (KS == 1 ? 2048 : 8192) ? 2 : 4; }
+
+// Whether decode_qkv_fwd forms z~ gamma first, in 256 x 256 tiles, instead of the
+// weights' product in strips of columns.  The workspace holds the row sums of n KS x 8
+// tokens (`chunk`); more tokens go in chunks of two launches each, which a narrow n
+// makes many, and a strip costs the same few microseconds however narrow n is:
+// strips against tiles 1278 and 17 us at 65536 x 64 x 192, r = 32, 357 and 66 at
+// 65536 x 256 x 768, 226 and 182 at 120000 x 1024 x 24, r = 64, 14.4 and 10.8 at
+// 5 x 64 x 9528, but 36 and 159 at 1024 x 4096 x 6144 and 61 and 158 at 16384 x 1024 x
+// 3072.  Both sides in microseconds, fitted to 445 shapes (n = 64 to 2048, T to 130000,
+// N = 8 to 48000; 7 and 9 % off at one sigma): the wrong side was at most 11 % slower.
+bool qkv_by_tiles(int64_t T, int n, int N, int KS, int64_t chunk) {
+  auto rounds = [](int64_t blocks) { return (double)((blocks + kNumBlocks - 1) / kNumBlocks); };
+  const double tiles = rounds(((T + 255) / 256) * ((N + 255) / 256)), chunks = (double)((T + chunk - 1) / chunk);
+  const int wc = 16 * qkv_ct(std::min(T, chunk), KS);
+  const double by_tiles = 8.0 + tiles * (1.1 + n / 64 * (KS == 1 ? 2.2 : 5.4)) + (double)T * N * 6.1e-7;
+  const double by_strips = chunks * (9.3 + (KS == 1 ? 0.0 : 4.1) + n * 0.0041 +
+                                     (rounds((N + wc - 1) / wc) - 1.0) * (4.7 + n * 0.0061)) +
+                           (double)T * (n * (KS == 1 ? 1.6e-7 : 7.1e-7) + N * 7.2e-7);
+  return by_tiles < by_strips;
 }
 
 template <int KS>
@@ -1948,6 +2157,19 @@ int32_t resbm_decode_qkv_fwd(int64_t T, int32_t n, int32_t r, int32_t N, const v
   g.ssq = (float*)ws;
   g.ld_out = ld_out;
   g.eps = eps;
+  if (qkv_by_tiles(T, n, N, KS, most)) {
+    hipLaunchKernelGGL(k_frag_prep, dim3((unsigned)(KS * (n / 16))), dim3(64), 0, st, W_d, r, n, (int64_t)n, n / 16,
+                       (__bf16*)ws);
+    g.T = (int)T;
+    g.b = (const __bf16*)b;
+    g.wf = (__bf16*)ws;
+    g.out = (__bf16*)out;
+    g.out_bytes = (int64_t)bo;
+    const unsigned tiles = (unsigned)(((T + 255) / 256) * ((N + 255) / 256));
+    if (KS == 1) hipLaunchKernelGGL(k_dec_qkv<1>, dim3(tiles), dim3(512), 0, st, g);
+    else hipLaunchKernelGGL(k_dec_qkv<2>, dim3(tiles), dim3(512), 0, st, g);
+    return resbm_host::launch_status();
+  }
   for (int64_t t0 = 0; t0 < T; t0 += most) {
     g.T = (int)std::min(most, T - t0);
     g.b = (const __bf16*)b + t0 * r;
@@ -1960,13 +2182,7 @@ int32_t resbm_decode_qkv_fwd(int64_t T, int32_t n, int32_t r, int32_t N, const v
     const size_t sq = round_up((size_t)g.ncg * g.T * 4, kWsAlign2);
     g.wf = (__bf16*)((char*)ws + sq);
     g.npre = (int)std::min<size_t>(n / 64, (need - sq) / (KS * 8192));
-    // 32-column strips while out is short (more blocks: 37.5 us either way at
-    // 1024 x 4096 x 6144, r = 32; 27.6 against 52.4 at 300 x 2112 x 4000, r = 64);
-    // beyond, 64-column ones write whole 128-byte lines (16384 x 4096 x 6144:
-    // 94 against 113 us).  Above r = 32 they win later, the narrower out is the
-    // later (r = 64: 85 and 83 us at 4096 x 4096 x 6144, 137 against 118 at 8192 rows;
-    // r = 48: 50 against 55 at 6000 x 2048 x 4000)
-    const int ct = g.T <= (KS == 1 ? 2048 : 8192) ? 2 : 4, strips = (N + 16 * ct - 1) / (16 * ct);
+    const int ct = qkv_ct(g.T, KS), strips = (N + 16 * ct - 1) / (16 * ct);
     // token ranges: blocks for the whole chip, one per compute unit (two: 74 against 44 us at 1024 rows)
     int ranges = std::max(1, std::min(kNumBlocks / strips, (g.T + 255) / 256));
     g.rows = (int)round_up((size_t)(g.T + ranges - 1) / ranges, 256);

@@ -1,7 +1,8 @@
 """The decoder fused into RMSNorm + QKV at the edges of its strips: column tails
 of 32- and 64-column strips, token tails, several token ranges, more rows than
-row scales held at a time, several chunks of tokens, units behind the prepared
-fragments, both depths of r; every workspace byte behind the required ones kept.
+row scales held at a time, units behind the prepared fragments, both depths of r
+(three shapes take the other order, in tiles: see test_gpu_qkv_tiles.py, which has
+the chunks of tokens too); every workspace byte behind the required ones kept.
 """
 import pytest
 import torch
