@@ -257,7 +257,9 @@ __global__ __launch_bounds__(64) void k_frag_prep(const float* __restrict__ W, i
 // multiplies rows 32 w .. 32 w + 31 of it by the tile's 256 rows of W_e
 // (float32, as hi + lo bf16 fragments prepared by k_frag_prep, in X), writing
 // the float32 partial sum D[tile column][row][0 .. r).  The partials are added
-// in tile order by k_enc_finish.
+// in tile order by k_enc_finish.  Columns of the tile at or beyond N hold products of
+// other W_down elements (HalfSrc::issue) and are staged as zeros: W_e's rows are zero
+// there, but an infinity among those products would make 0 x inf of every a.
 __device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (&acc)[8][4], __bf16* tile, int m0,
                                                 int n0) {
   constexpr int BN = 256;
@@ -271,9 +273,10 @@ __device__ __forceinline__ void encode_epilogue(const GemmArgs& g, const f32x4 (
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int nl = (j >> 1) * 128 + wn * 32 + (j & 1) * 16 + 4 * grp;
+      const bool on = n0 + nl < g.N;  // N % 8 == 0: all four or none
       bf16x4 h;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) h[e] = (__bf16)acc[i][j][e];
+      for (int e = 0; e < 4; ++e) h[e] = (__bf16)(on ? acc[i][j][e] : 0.0f);
       *reinterpret_cast<uint2*>(tile + ml * 256 + resbm::wide_col(ml, nl)) = __builtin_bit_cast(uint2, h);
     }
   }
@@ -359,7 +362,8 @@ struct HalfSrc {
   // the stage's start (chunks at or beyond it become zeros).  Indices past the
   // operand's extent need no test: a K-contiguous row past the last lies outside
   // the descriptor, and a column past the last holds some other element of the
-  // operand, which only reaches outputs that are not stored.
+  // operand, which only reaches elements of the tile that are not part of the
+  // result: they are not stored, and encode_epilogue leaves them out.
   __device__ __forceinline__ void issue(rsrc_t src, int h, int krem, __bf16* half, int wave) const {
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
