@@ -534,15 +534,26 @@ __device__ __forceinline__ Item item_of(const GemmArgs& g, int i) {
   return it;
 }
 
+// The descriptor of the result for a tile that starts at row m0.  A float32 weight
+// gradient may take 8 GiB (its bf16 weight up to 4), so its descriptor starts at that
+// row; the others cover the whole result: T-row ones and intermediates are below
+// 4 GiB by the shape rules, partial sums below 512 x 256 KiB by split_for.
+template <int EPI>
+__device__ __forceinline__ rsrc_t out_desc(const GemmArgs& g, int m0) {
+  const int64_t skip = EPI == kEpiF32 ? (int64_t)m0 * g.ldc * 4 : 0;
+  return make_rsrc((const char*)g.C + skip, g.c_bytes - skip);
+}
+
 // Stores four consecutive columns n .. n + 3 of row m of the result with the
 // epilogue EPI (out of range: dropped).  Offsets of elements in range are below
-// 4 GiB, so 32-bit arithmetic is exact for them.
+// 4 GiB, so 32-bit arithmetic is exact for them (kEpiF32: from row m0 on).
 template <int EPI>
-__device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m, int n,
-                                         f32x4 v) {
+__device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m0, int m,
+                                         int n, f32x4 v) {
   const bool ok = m < g.M && n < g.N;
   if constexpr (EPI == kEpiF32 || EPI == kEpiPart) {
-    const uint32_t off = EPI == kEpiPart ? ((uint32_t)split * g.M + m) * g.N + n : (uint32_t)m * (uint32_t)g.ldc + n;
+    const uint32_t off =
+        EPI == kEpiPart ? ((uint32_t)split * g.M + m) * g.N + n : (uint32_t)(m - m0) * (uint32_t)g.ldc + n;
     bst16(rc, ok ? off * 4 : kOOB, __builtin_bit_cast(uint4, v));
   } else {
     if constexpr (EPI == kEpiDphi || EPI == kEpiAdd) {
@@ -577,11 +588,11 @@ constexpr int pair_stores(int epi) { return epi == kEpiF32 || epi == kEpiPart ||
 // store instructions, 64 bytes of a row each instead of 32 (the two-linear step at
 // 16384 x 4096 x 1024: 872 -> 836 us).
 template <int EPI>
-__device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m, int n,
-                                           int grp, f32x4 v0, f32x4 v1) {
+__device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m0,
+                                           int m, int n, int grp, f32x4 v0, f32x4 v1) {
   if constexpr (EPI == kEpiF32 || EPI == kEpiPart) {
-    store_c4<EPI>(g, rc, rx, rd, split, m, n, v0);
-    store_c4<EPI>(g, rc, rx, rd, split, m, n + 16, v1);
+    store_c4<EPI>(g, rc, rx, rd, split, m0, m, n, v0);
+    store_c4<EPI>(g, rc, rx, rd, split, m0, m, n + 16, v1);
   } else {
     f32x4 v[2] = {v0, v1};
     const int c8 = n - 4 * (grp & 1) + 16 * (grp & 1);  // n = ... + 4 grp
@@ -783,7 +794,7 @@ __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
   phase_barrier();
   if (wm == 1) phase_barrier();  // waves 4-7 run one section behind
 
-  const rsrc_t rc = make_rsrc(g.C, g.c_bytes), rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
+  const rsrc_t rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
   bool stored = false;
   for (;;) {
     const int npair = (cur.klen + 2 * KT - 1) / (2 * KT);
@@ -801,12 +812,13 @@ __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
       pair(stored && p == 0);
     }
     if constexpr (EPI != kEpiEncode) {
+      const rsrc_t rc = out_desc<EPI>(g, cur.m0);
       const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-          store_pair<EPI>(g, rc, rx, rd, cur.split, mr + (i >> 2) * 128 + (i & 3) * 16, nr + q * 128, grp,
+          store_pair<EPI>(g, rc, rx, rd, cur.split, cur.m0, mr + (i >> 2) * 128 + (i & 3) * 16, nr + q * 128, grp,
                           acc[i][2 * q], acc[i][2 * q + 1]);
     }
     if (EPI == kEpiEncode || !more) break;
@@ -817,11 +829,12 @@ __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
   if (wm == 0) phase_barrier();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if constexpr (EPI == kEpiEncode) {
+    const rsrc_t rc = out_desc<EPI>(g, cur.m0);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int q = 0; q < 2; ++q)
-        store_pair<kEpiBf16>(g, rc, rx, rd, 0, cur.m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + row16,
+        store_pair<kEpiBf16>(g, rc, rx, rd, 0, 0, cur.m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + row16,
                              cur.n0 + q * 128 + wn * 32 + 4 * grp, grp, acc[i][2 * q], acc[i][2 * q + 1]);
     encode_epilogue(g, acc, smem, cur.m0, cur.n0);
   }
@@ -886,7 +899,7 @@ __global__ __launch_bounds__(512) void k_gemm_mid(GemmArgs g, int total) {
   phase_barrier();
   if (wm == 1) phase_barrier();  // waves 4-7 run one section behind
 
-  const rsrc_t rc = make_rsrc(g.C, g.c_bytes), rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
+  const rsrc_t rx = make_rsrc(g.X, g.x_bytes), rd = make_rsrc(g.D, g.d_bytes);
   int slot = 0;
   bool stored = false;
   for (;;) {
@@ -910,10 +923,11 @@ __global__ __launch_bounds__(512) void k_gemm_mid(GemmArgs g, int total) {
       phase_barrier();
       slot = (slot + 1) & 3;
     }
+    const rsrc_t rc = out_desc<EPI>(g, cur.m0);
     const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      store_pair<EPI>(g, rc, rx, rd, cur.split, mr + 16 * i, nr, grp, acc[i][0], acc[i][1]);
+      store_pair<EPI>(g, rc, rx, rd, cur.split, cur.m0, mr + 16 * i, nr, grp, acc[i][0], acc[i][1]);
     wl.next += wl.stride;
     if (wl.next >= wl.end) break;
     stored = true;
@@ -996,14 +1010,14 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs g) {
   }
 
   // lane (row16, grp) of tile (i, j) holds C[m][n .. n + 3]
-  const rsrc_t rc = make_rsrc(g.C, g.c_bytes);
+  const rsrc_t rc = out_desc<EPI>(g, m0);
   const rsrc_t rx = make_rsrc(g.X, g.x_bytes);
   const rsrc_t rd = make_rsrc(g.D, g.d_bytes);
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j)
-      store_c4<EPI>(g, rc, rx, rd, blockIdx.z, m0 + (wm * FM + i) * 16 + row16, n0 + (wn * FN + j) * 16 + 4 * grp,
+      store_c4<EPI>(g, rc, rx, rd, blockIdx.z, m0, m0 + (wm * FM + i) * 16 + row16, n0 + (wn * FN + j) * 16 + 4 * grp,
                     acc[i][j]);
 }
 
