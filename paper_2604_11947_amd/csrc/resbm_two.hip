@@ -556,14 +556,20 @@ __device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx
         EPI == kEpiPart ? ((uint32_t)split * g.M + m) * g.N + n : (uint32_t)(m - m0) * (uint32_t)g.ldc + n;
     bst16(rc, ok ? off * 4 : kOOB, __builtin_bit_cast(uint4, v));
   } else {
-    if constexpr (EPI == kEpiDphi || EPI == kEpiAdd) {
-      const bool xok = ok && (EPI == kEpiDphi || n < g.x_cols);
+    if constexpr (EPI == kEpiDphi || EPI == kEpiDphiPhi || EPI == kEpiAdd) {
+      const bool xok = ok && (EPI != kEpiAdd || n < g.x_cols);
       const uint2 xr = bld8(rx, xok ? ((uint32_t)m * (uint32_t)g.ldx + n) * 2 : kOOB);
       const bf16x4 x = __builtin_bit_cast(bf16x4, xr);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if constexpr (EPI == kEpiDphi) v[e] *= resbm::silu_grad((float)x[e]);
-        else v[e] += (float)x[e];
+        if constexpr (EPI == kEpiAdd) v[e] += (float)x[e];
+        else v[e] *= resbm::silu_grad((float)x[e]);
+      }
+      if constexpr (EPI == kEpiDphiPhi) {
+        bf16x4 p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = (__bf16)silu((float)x[e]);
+        bst8(rd, ok ? ((uint32_t)m * (uint32_t)g.ldd + n) * 2 : kOOB, __builtin_bit_cast(uint2, p));
       }
     }
     bf16x4 h;
@@ -938,9 +944,10 @@ __global__ __launch_bounds__(512) void k_gemm_mid(GemmArgs g, int total) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// C = A B for the r-wide results (64 x {32, 64, 128} tiles), staged through
-// registers, double buffered, one barrier per 64-deep stage; PHI_A applies SiLU
-// to A's elements as they are staged.
+// C = A B in tiles of 64 x {32, 64, 128} (the r-wide results, and T-row products
+// whose 128 x 128 tiles would leave most of the chip idle) or 128 x 128 by four waves,
+// staged through registers, double buffered, one barrier per 64-deep stage; PHI_A
+// applies SiLU to A's elements as they are staged.
 template <bool AK, bool BKC, int BM, int BN, int WM, int WN, int EPI, bool PHI_A>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm(GemmArgs g) {
   constexpr int NTH = 64 * WM * WN;
@@ -1683,29 +1690,46 @@ bool shape_ok2(int64_t T, int n, int m, int r) {
 }
 bool fits(size_t bytes) { return bytes <= (size_t)kMaxRange; }
 
-// Block tile shapes: 256 x 256 and 128 x 128 for the n x m products (the
-// pipelined kernels), and a narrow one for an r-wide output (N = r).  Products
-// with M = r use 128 x 128; the rows beyond r only reach discarded outputs.
-enum Shape { kBig = 0, kWide = 1, kNarrow32 = 2, kNarrow64 = 3, kNarrow128 = 4 };
+// Block tile shapes: 256 x 256 and 128 x 128 (the pipelined kernels), 128 x 128 by
+// four waves (64 KiB of LDS: two blocks per unit) and narrow ones.  Products with
+// M = r use 128 x 128; the rows beyond r only reach discarded outputs.
+enum Shape { kBig = 0, kWide = 1, kNarrow32 = 2, kNarrow64 = 3, kNarrow128 = 4, kFour = 5 };
 
 // Weight gradients: 256 x 256 unless M or N is below it (their token splits
 // fill the chip either way).
 Shape wide_for(int M, int N) { return M >= 256 && N >= 256 ? kBig : kWide; }
-// T-row products (no split): a 64-deep stage of a full round of 256 blocks takes
-// 1.4 us in 256 x 256 tiles and 0.7 in 128 x 128 ones (a quarter of the work,
-// twice the operand bytes per product), so the small tiles win where they need
-// fewer than twice the rounds, i.e. where at most 64 large tiles would leave
-// most of the chip idle (1024 x 4096 x 14336: 161 against 258 us; 4096 x 4096 x
-// 14336, 256 large tiles: 582 against 343), and where half a large tile would be padding.
-Shape rows_for(int M, int N) {
-  const int64_t big = ((int64_t)(M + 255) / 256) * ((N + 255) / 256), mid = ((int64_t)(M + 127) / 128) * ((N + 127) / 128);
-  const int64_t rb = (big + 255) / 256, rm = (mid + 255) / 256;
-  return M <= 128 || N <= 128 || rm < 2 * rb ? kWide : kBig;
-}
 Shape narrow_for(int N) { return N <= 32 ? kNarrow32 : (N <= 64 ? kNarrow64 : kNarrow128); }
-int shape_bm(Shape s) { return s == kBig ? 256 : (s == kWide ? 128 : 64); }
+// T-row products (no split).  Times below: encode2_fwd with r = 8 and the identity,
+// whose second product takes about 3 us; every line compares all the shapes on 800
+// random (M, N, K).
+//  - N <= 64, or at most 128 tiles of 128 x 128: 64 x 32 and 64 x 64 tiles.  More
+//    blocks, and no pipeline to fill: 1 x 8 x 8 5.4 us against 6.6 (128 x 128) and 9.3
+//    (256 x 256), 8029 x 256 x 2040 28.5 against 31.0 and 47.7, 22 x 504 x 3984 34.5
+//    against 47.5; beyond, their operand traffic costs (57388 x 440 x 472: 73 against 48).
+//  - N < 256: tiles as wide as N need the pipelined 128 x 128 kernel up to one round
+//    of blocks (23033 x 120 x 2072: 30.4 against 38.2 in narrow tiles), the four-wave
+//    one beyond, whose two blocks per unit hold two rounds' tiles at once (53966 x 120 x
+//    752: 28.9 against 29.7 and 31.1 in 256 x 256; 19040 x 176 x 152: 12.8, 13.8 and
+//    15.1), and 256 x 256 from three rounds on if N > 128 (34600 x 160 x 416: 23.5
+//    against 28.0 and 27.0).
+//  - else a 64-deep stage of a full round of 256 blocks takes 1.4 us in 256 x 256
+//    tiles and 0.7 in 128 x 128 ones (a quarter of the work, twice the operand bytes per
+//    product), so the small tiles win where they need fewer than twice the rounds, i.e.
+//    where at most 64 large tiles would leave most of the chip idle (1024 x 4096 x
+//    14336: 161 against 258 us; 4096 x 4096 x 14336, 256 large tiles: 582 against 343);
+//    where half a large tile would be padding; and where there is one stage (a pair of stages is the large tiles' step; 35631 x
+//    464 x 32: 22.2 against 25.1).
+Shape rows_for(int M, int N, int K) {
+  const int64_t big = ((int64_t)(M + 255) / 256) * ((N + 255) / 256), mid = ((int64_t)(M + 127) / 128) * ((N + 127) / 128);
+  const int64_t rb = (big + kNumBlocks - 1) / kNumBlocks, rm = (mid + kNumBlocks - 1) / kNumBlocks;
+  if (N <= 32) return kNarrow32;
+  if (N <= 64 || mid <= kNumBlocks / 2) return kNarrow64;
+  if (N < 256) return rm <= 1 ? kWide : (N <= 128 || rm <= 2 ? kFour : kBig);
+  return K <= KT || M <= 128 || rm < 2 * rb ? kWide : kBig;
+}
+int shape_bm(Shape s) { return s == kBig ? 256 : (s == kWide || s == kFour ? 128 : 64); }
 int shape_bn(Shape s) {
-  return s == kBig ? 256 : (s == kWide || s == kNarrow128 ? 128 : (s == kNarrow32 ? 32 : 64));
+  return s == kBig ? 256 : (s == kWide || s == kFour || s == kNarrow128 ? 128 : (s == kNarrow32 ? 32 : 64));
 }
 
 struct Split {
@@ -1766,18 +1790,19 @@ void launch_mid(const GemmArgs& g, int S, hipStream_t st) {
   hipLaunchKernelGGL((k_gemm_mid<AK, BKC, EPI>), dim3(std::min(total, kNumBlocks)), dim3(512), 0, st, g, total);
 }
 
-// Runs C = op(A) op(B) with the epilogue EPI and tile shape s.
+// Runs C = op(A) op(B) with the epilogue EPI and tile shape s.  PHI is the dW2
+// product's, whose tiles are narrow; 64 x 128 ones are r-wide results only.
 template <bool AK, bool BKC, int EPI, bool PHI>
 void gemm(Shape s, const GemmArgs& g, int S, hipStream_t st) {
   if constexpr (!PHI) {
     if (s == kBig) return launch_big<AK, BKC, EPI>(g, S, st);
     if (s == kWide) return launch_mid<AK, BKC, EPI>(g, S, st);
+    if (s == kFour) return launch<AK, BKC, 128, 128, 2, 2, EPI, false>(g, S, st);
   }
-  switch (s) {
-    case kNarrow32: launch<AK, BKC, 64, 32, 4, 1, EPI, PHI>(g, S, st); break;
-    case kNarrow64: launch<AK, BKC, 64, 64, 4, 1, EPI, PHI>(g, S, st); break;
-    default: launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st); break;
-  }
+  if (s == kNarrow32) return launch<AK, BKC, 64, 32, 4, 1, EPI, PHI>(g, S, st);
+  if (s == kNarrow64) return launch<AK, BKC, 64, 64, 4, 1, EPI, PHI>(g, S, st);
+  if constexpr (EPI == kEpiBf16 || EPI == kEpiAdd || EPI == kEpiF32 || EPI == kEpiPart)
+    launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st);
 }
 
 GemmArgs args(int M, int N, int K, const void* A, int64_t lda, size_t ab, const void* B, int64_t ldb, size_t bb,
@@ -1793,9 +1818,15 @@ GemmArgs args(int M, int N, int K, const void* A, int64_t lda, size_t ab, const 
 
 // A token-deep weight-gradient product (K = T): float32 result W (M x N,
 // contiguous), split over tokens with the partial sums in `part` when that
-// fills the chip better.
+// fills the chip better.  128 x 128 tiles take the four-wave kernel where its two
+// blocks per unit save a second round (decode2_bwd 34580 x 2880 x 40 x 16, 23 tiles
+// in 12 splits: 121.7 against 138.8 us; 49261 x 488 x 144 x 8, 256 items: 121.7 against
+// 103.9) and where there are at most three stages, too few to fill the pipeline (T =
+// 8: 11.5 against 12.5 us; T = 157: 14.7 and 15.5; T = 411: 21.5 and 20.8).
 template <bool PHI>
 void weight_grad(Shape s, GemmArgs g, const Split& sp, float* W, void* part, hipStream_t st) {
+  if (s == kWide && ((int64_t)sp.S * ((g.M + 127) / 128) * ((g.N + 127) / 128) > kNumBlocks || sp.kc <= 3 * KT))
+    s = kFour;
   if (sp.S == 1) {
     g.C = W; g.ldc = g.N; g.c_bytes = (int64_t)g.M * g.N * 4;
     gemm<false, false, kEpiF32, PHI>(s, g, 1, st);
@@ -1894,9 +1925,9 @@ int32_t resbm2_encode_fwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, n, z, ld_z, bz, W1, m, bw1, u, m, bu);
   if (silu) {
     g.D = ws; g.ldd = m; g.d_bytes = (int64_t)bu;
-    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m, n), g, 1, st);
   } else {
-    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m, n), g, 1, st);
   }
   // b = x_attn[:, :r] + phi(u) W2
   g = args(Ti, r, m, silu ? ws : u, m, bu, W2, r, bw2, b, r, bb);
@@ -1934,13 +1965,13 @@ int32_t resbm2_decode_fwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, r, b, r, bb, W3, m, bw3, v, m, bv);
   if (silu) {
     g.D = ws; g.ldd = m; g.d_bytes = (int64_t)bv;
-    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16Phi, false>(rows_for(Ti, m, r), g, 1, st);
   } else {
-    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, false, kEpiBf16, false>(rows_for(Ti, m, r), g, 1, st);
   }
   // z~ = phi(v) W4
   g = args(Ti, n, m, silu ? ws : v, m, bv, W4, n, bw4, z_tilde, ld_zt, bzt);
-  gemm<true, false, kEpiBf16, false>(rows_for(Ti, n), g, 1, st);
+  gemm<true, false, kEpiBf16, false>(rows_for(Ti, n, m), g, 1, st);
   return resbm_host::launch_status();
 }
 
@@ -1986,9 +2017,9 @@ int32_t resbm2_decode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
     // and phi(v), from the v that the epilogue reads (16384 x 1024: a launch of 10.8 us)
     g.X = v; g.ldx = m; g.x_bytes = (int64_t)bv;
     g.D = pv; g.ldd = m; g.d_bytes = (int64_t)bv;
-    gemm<true, true, kEpiDphiPhi, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiDphiPhi, false>(rows_for(Ti, m, n), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m, n), g, 1, st);
   }
   // dW4 = phi(v)^T g_zt   (A(i, k) = phi(v)[k][i], B(k, j) = g_zt[k][j])
   g = args(m, n, Ti, silu ? pv : v, m, bv, g_zt, ld_gzt, bg, nullptr, 0, 0);
@@ -2049,9 +2080,9 @@ int32_t resbm2_encode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   GemmArgs g = args(Ti, m, r, g_b, r, bgb, W2, r, bw2, g_u, m, bu);
   if (silu) {
     g.X = u; g.ldx = m; g.x_bytes = (int64_t)bu;
-    gemm<true, true, kEpiDphi, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiDphi, false>(rows_for(Ti, m, r), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, m, r), g, 1, st);
   }
   // dW2 = phi(u)^T g_b
   g = args(m, r, Ti, u, m, bu, g_b, r, bgb, nullptr, 0, 0);
@@ -2064,9 +2095,9 @@ int32_t resbm2_encode_bwd(int64_t T, int32_t n, int32_t m, int32_t r, int32_t ac
   g = args(Ti, n, m, g_u, m, bu, W1, m, bw1, g_z, ld_gz, bgz);
   if (fused) {
     g.X = g_b; g.ldx = r; g.x_bytes = (int64_t)bgb; g.x_cols = r;
-    gemm<true, true, kEpiAdd, false>(rows_for(Ti, n), g, 1, st);
+    gemm<true, true, kEpiAdd, false>(rows_for(Ti, n, m), g, 1, st);
   } else {
-    gemm<true, true, kEpiBf16, false>(rows_for(Ti, n), g, 1, st);
+    gemm<true, true, kEpiBf16, false>(rows_for(Ti, n, m), g, 1, st);
     if (g_x) {
       const int64_t cnt = T * (r / 4);
       hipLaunchKernelGGL(k_skip_grad, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, T, r,
