@@ -18,12 +18,12 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # T, n, m, r
     (255, 264, 256, 8),       # one 128-tile row short of two
-    (257, 512, 264, 32),      # a row past, K of 9 stages (odd) and 5
-    (1030, 264, 520, 40),     # 128 x 128 tiles, ragged both ways
+    (257, 512, 264, 32),      # a row past, K of 8 stages and of 5
+    (1030, 264, 520, 40),     # 64 x 64 tiles, ragged both ways; dW4 and dW1 in 256 x 256
     (4360, 4104, 72, 8),      # 306 tiles of 256 x 256 on 256 blocks, K = 72 (one stage pair)
     (8200, 2312, 200, 24),    # 330 tiles, K = 200 (four stages)
-    (40000, 72, 128, 16),     # 313 tiles of 128 x 128 on 256 blocks
-    (33000, 64, 8, 8),        # one stage per item: the ring runs across items
+    (40000, 72, 128, 16),     # 313 tiles of 128 x 128 by four waves
+    (33000, 64, 8, 8),        # 64 x 32 and 64 x 64 tiles, one stage
 ]
 
 
