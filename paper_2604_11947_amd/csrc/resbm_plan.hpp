@@ -172,17 +172,40 @@ constexpr int rw_ntw(int NT) {
 // MT = 4 doubles what a block's split of W_e is spread over, and pays while
 // that split is small, n x 16 JT <= 65536 values:
 //   T = 16384, n = 2048, r = 16: 16.1 -> 14.2 us; T = 32768, n = 1024, r = 4: 18.8 -> 14.2.
+// With more blocks than compute units (two per unit) only where r takes one of the
+// streaming kernel's narrow tilings and, above r = 16, n is narrow:
+//   T = 14558, n = 512, r = 84: 14.8 -> 21.2 us; T = 13396, n = 1024, r = 88: 19.5 -> 28.5;
+//   r = 32 at n = 768 and 832: 17.1 -> 16.5, 18.1 -> 19.4 (T = 30000); r = 16, n = 960: 18.1 -> 14.6.
 constexpr int kEfShortMt4 = 65536;
-// decode_bwd and encode_bwd: 64 x 256 tiles, streams of at most 2^25 elements:
+constexpr int kEfShortMt4N = 768;
+// decode_bwd and encode_bwd: 64 x 256 tiles, streams of at most 2^25 elements (the
+// columns counted in whole tiles: T = 29448, n = 1088 = 4.25 tiles, r = 40 ran decode_bwd
+// 43.6 -> 47.6 us):
 //   decode_bwd, r = 32, n = 4096: T = 1024 25.9 -> 16.6 us, T = 8192 33.5 -> 25.8, T = 16384 44.0 and 46.6;
 //   encode_bwd, r = 32, n = 4096: T = 1024 19.8 -> 15.4 us, T = 8192 35.7 -> 31.8, T = 16384 56.4 and 60.2.
 constexpr int64_t kOnceElems = (int64_t)1 << 25;
+// encode_bwd: each block splits g_h and W_e for 256 columns, which the streaming
+// kernels' g_z pass does once per token group, so long token ranges lose:
+//   T = 16384 and below: n = 64, r = 64: 20.8 -> 16.9 us (T = 15806);
+//   n = 64: T = 17658, r = 32 14.4 -> 16.3; T = 29663, r = 40 19.6 -> 28.7; n = 448, T = 50960,
+//   r = 36 42.2 -> 55.7; but up to r = 32 and 32768 tokens n >= 192 keeps its gain:
+//   n = 320, T = 17368 22.7 -> 19.5; n = 256, T = 26164 22.6 -> 19.5; T = 53011, n = 192 24.7 -> 25.9.
+constexpr int64_t kOnceEbTokens = 16384;
 constexpr int short_jt(int NT) { return NT <= 2 ? NT : 4; }  // j-tiles per block
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 inline size_t align_ws(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; }
 inline int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// 64-token steps per block of the short backward ops, for `tiles` of them in each of
+// `cols` column groups: as many as leave a block per compute unit, and from four on
+// no block more than there are units (a few more would take a round of their own).
+inline int64_t once_steps(int64_t tiles, int64_t cols) {
+  int64_t per = clamp64(tiles * cols / kNumCU, 1, tiles);
+  while (per >= 4 && ceil_div(tiles, per) * cols > kNumCU && per < tiles) ++per;
+  return per;
+}
 
 struct Plan {
   int64_t T;
@@ -307,7 +330,8 @@ inline Plan make_plan(int64_t T, int n, int r) {
   const int64_t jg = ceil_div(p.NT, short_jt(p.NT));
   for (int mt = 1; mt <= 4 && !p.ef_smt; mt *= 2) {
     const int64_t blocks = ceil_div(Tm, 16 * mt) * jg;
-    if (mt == 4 ? blocks <= 2 * kNumCU && n * 16 * short_jt(p.NT) <= kEfShortMt4
+    if (mt == 4 ? (blocks <= kNumCU || (blocks <= 2 * kNumCU && p.NT <= 4 && (p.NT == 1 || n <= kEfShortMt4N))) &&
+                      n * 16 * short_jt(p.NT) <= kEfShortMt4
                 : blocks < kNumCU || (mt == 2 && blocks == kNumCU)) {
       p.ef_smt = mt;
       int64_t most = n / 512;            // at least one 64-column unit per wave and slice
@@ -317,20 +341,20 @@ inline Plan make_plan(int64_t T, int n, int r) {
   }
   // steps per block of the backward ops: as many as leave a block per compute
   // unit, and enough for the partial sums of the token groups to fit
-  if (Tm * n <= kOnceElems) {
+  if (Tm * round_up(n, 256) <= kOnceElems) {
     const int64_t tiles = ceil_div(Tm, 64);
     const size_t dw1 = (size_t)p.RP * n * 4;  // one token group's partials
     p.once_ncg = (int)ceil_div(n, 256);
     const size_t gb = align_ws((size_t)p.once_ncg * Tm * p.RP * 4);
     const int64_t fit = p.db_ws > gb ? (int64_t)((p.db_ws - gb) / dw1) : 0;
-    const int64_t per = clamp64(tiles * p.once_ncg * jg / kNumCU, 1, tiles);
+    const int64_t per = once_steps(tiles, p.once_ncg * jg);
     // (decode_bwd, wide r: a fit of few groups would leave the chip idle)
     if (fit >= ceil_div(tiles, per) || fit * p.once_ncg * jg >= kNumCU / 2) {
       p.db_once = (int)(ceil_div(tiles, per) <= fit ? per : ceil_div(tiles, fit));
       p.db_once_dwp = gb;
     }
-    if (!p.wide) {
-      const int64_t fe = (int64_t)(p.eb_ws / dw1), pe = clamp64(tiles * p.once_ncg / kNumCU, 1, tiles);
+    if (!p.wide && (T <= kOnceEbTokens || (T <= 2 * kOnceEbTokens && p.NT <= 2 && n >= 192))) {
+      const int64_t fe = (int64_t)(p.eb_ws / dw1), pe = once_steps(tiles, p.once_ncg);
       p.eb_once = (int)(ceil_div(tiles, pe) <= fe ? pe : ceil_div(tiles, fe));
     }
   }
