@@ -10,8 +10,9 @@ encode_bwd's g_z multiplies the split g_h by the split W_e (three products),
 so an infinite weight also meets g_h's lo part (inf * 0, or an opposite sign)
 and those entries come out NaN where the oracle has +-inf; there only the set
 of non-finite entries must match.  Shapes cover the
-in-kernel weight split (r = 16), the prepared fragments (r = 32) and the
-wide-rank kernels (r = 128).
+one-pass kernels of short streams (r = 16, 32 and 128) and, for decode_fwd and
+encode_bwd, the wide-rank ones (r = 128); test_gpu_streaming.py runs the same checks
+on the streaming kernels.
 """
 import numpy as np
 import pytest

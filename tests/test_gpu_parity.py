@@ -21,15 +21,18 @@ ID, SILU = O.ACT_IDENTITY, O.ACT_SILU
 
 # (T, n, r): several tiles in every direction, ragged token tails, r not a
 # multiple of 16 (4, 12, 40, 100, 136), full rank (r = n), the largest r, and
-# the wide-rank kernels (r > 64) at odd tile counts.
+# r > 64 at odd tile counts.  encode_fwd, decode_bwd and (r <= 64) encode_bwd run the
+# one-pass kernels of short streams here; test_gpu_streaming.py has the streaming
+# ones, and the comments below say what a shape is in those: the wide-rank kernels
+# that decode_fwd and encode_bwd take above r = 64 in any case.
 SHAPES = [(1000, 512, 32), (777, 256, 4), (333, 320, 40), (517, 1024, 64), (45, 192, 12),
           (130, 128, 128), (96, 256, 256), (64, 64, 64), (1, 64, 4),
           # wide rank (r > 64): r % 8 == 4, r a multiple of 16, 48, 64, odd tile counts, n % 128 == 64, T = 1
           (333, 768, 100), (700, 576, 136), (1000, 1024, 192), (64, 256, 80), (1, 128, 128),
-          # row contraction with r split over two blocks: one token, one group plus one token
+          # r of more than eleven tiles: one token, one 128-token group plus one token
           (1, 256, 200), (129, 512, 256),
-          # token contraction in 64-token steps: 96-token groups (a step and a half) and a
-          # ragged last group (28 and 24 tokens), with and without the split operand at its LDS limit
+          # token contraction (encode_bwd) in 64-token steps: 96-token groups (a step and a half)
+          # and a ragged last group (28 and 24 tokens), without and with the split operand at its LDS limit
           (700, 4096, 136), (600, 4096, 256),
           # the remaining rank tilings (16-column tiles of r: 6, 10, 11, 14, 15), two with a ragged last tile
           (257, 512, 92), (130, 640, 160), (65, 384, 176), (200, 1024, 224), (97, 768, 236),

@@ -21,6 +21,9 @@ CASES = [
     (4081, 512, 20, 0, False, False),   # first 32-token blocks
     (8192, 576, 12, 1, True, True),     # last 32-token blocks
     (8193, 576, 16, 1, False, False),   # first 64-token blocks; several steps per backward block
+    (16400, 768, 40, 1, False, True),   # more 64-token blocks than units; encode_bwd streams
+    (3572, 6592, 4, 1, True, False),    # decode_bwd: steps rounded up to one round of blocks
+    (32768, 192, 28, 0, False, True),   # encode_bwd: the longest token range
     (8193, 2112, 32, 1, False, True),   # encode_fwd back on the streaming kernel
     (16385, 2112, 20, 1, False, False),  # all ops on the streaming kernels (more than 2^25 elements)
     (2049, 1024, 132, 1, False, True),  # wide r: 32-token blocks, decode_bwd in three j-groups

@@ -86,3 +86,11 @@ EDGES = [
 @pytest.mark.parametrize("op,inside,outside", EDGES)
 def test_edges_of_the_rules(plan, op, inside, outside):
     assert plan(*inside)[op] > 0 and plan(*outside)[op] == 0
+
+
+def test_streaming_shapes_reach_the_streaming_kernels(plan):
+    import test_gpu_streaming as S
+
+    for op, shapes in (("encode_fwd", S.ENCODE_FWD), ("decode_bwd", S.DECODE_BWD), ("encode_bwd", S.ENCODE_BWD)):
+        for s in shapes:
+            assert plan(*s[:3])[op] == 0, (op, s)
