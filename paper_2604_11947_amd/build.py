@@ -21,6 +21,7 @@ DEPS = [SRC, SRC_MATRIX, SRC_TWO, os.path.join(PKG, "csrc", "resbm_buffer.hpp"),
         os.path.join(ROOT, "include", "resbm.h")]
 
 SRC_MARSHAL = os.path.join(PKG, "csrc", "resbm_marshal.cpp")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 LIBS = {"bf16": "libresbm.so", "f32": "libresbm_f32.so"}
 
@@ -63,7 +64,7 @@ def build_all(verbose: bool = False) -> list[str]:
     """Compile both variants and the marshalling module (in parallel); raises on any compiler error."""
     procs = []
     jobs = [(os.path.join(PKG, name), lambda tmp, v=variant: command(v, tmp)) for variant, name in LIBS.items()]
-    jobs.append((os.path.join(PKG, "_marshal.so"), marshal_command))
+    jobs.append((MARSHAL, marshal_command))
     for out, make in jobs:
         tmp = out + ".tmp"
         cmd = make(tmp)
@@ -90,11 +91,9 @@ def build_all(verbose: bool = False) -> list[str]:
 
 
 def up_to_date(variant: str = "bf16") -> bool:
-    out = lib_path(variant)
-    if not os.path.exists(out):
-        return False
-    t = os.path.getmtime(out)
-    return all(os.path.getmtime(d) <= t for d in DEPS)
+    """Whether the library variant and the marshalling module are no older than their sources."""
+    return all(os.path.exists(out) and all(os.path.getmtime(d) <= os.path.getmtime(out) for d in deps)
+               for out, deps in ((lib_path(variant), DEPS), (MARSHAL, [SRC_MARSHAL])))
 
 
 if __name__ == "__main__":

@@ -9,16 +9,21 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
 from . import build as _build
 
-try:  # native argument marshalling of the short ops; the Python path below does the same checks
-    from . import _marshal
-    _marshal.init(torch._C._cuda_getCurrentRawStream)
-except (ImportError, AttributeError):
-    _marshal = None
+# Native argument marshalling of the short ops; the Python path below does the same checks.
+_marshal = None
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    try:
+        from . import _marshal
+        _marshal.init(torch._C._cuda_getCurrentRawStream)
+    except ImportError as e:
+        warnings.warn(f"native argument marshalling not loaded ({e}): every op costs about 9 us more of host time; "
+                      "run `python -m paper_2604_11947_amd.build`", RuntimeWarning)
 
 ACT_IDENTITY = 0
 ACT_SILU = 1
