@@ -377,9 +377,11 @@ def optimizer_timing(lib, d: dict, r: int, dev, iters: int, cpu: bool) -> dict:
         return e0.elapsed_time(e1) * 1e3 / iters
 
     steps = 5
-    # short side <= 64: load + Gram, ordered sum, the recurrence on the s x s Gram
-    # (one block), output pass; wider: load, then per step reduce + poly + row update
-    launches = 4 if r <= 64 else 1 + 3 * steps
+    # short side <= 64: partial Grams of 128-row chunks, the recurrence on the s x s Gram
+    # (one block, which adds up to 512 KiB of partials itself; more are one launch
+    # more), output pass; wider: load, then per step reduce + poly + row update
+    partials = -(-n // 128) * (-(-r // 4) * 4) ** 2
+    launches = (3 if partials <= 65536 else 4) if r <= 64 else 1 + 3 * steps
     out = {"ns_steps": steps, "coefficients": list(R.NS_QUINTIC),
            "launches_per_update": launches,
            "timing": "hip graph replay of one call", "iterations": iters}
@@ -556,7 +558,7 @@ def ffn_encode_timing(lib, d: dict, r: int, d_ff: int, dev, iters: int, act: int
            "fused_over_unfused": us["fused"] / us["unfused"], "iterations": iters,
            "timing": "HIP events around each call; unfused = the library GEMM and resbm_encode_fwd back to back",
            "tokens_per_s": T / (us["fused"] * 1e-6),
-           "roofline": {"bound": "mfma", "kernel": "k_gemm<256x256, encoder epilogue>", "achieved": tf,
+           "roofline": {"bound": "mfma", "kernel": "k_gemm_big with the encoder epilogue", "achieved": tf,
                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS,
                         "flops": flops}}
     if cpu:

@@ -359,8 +359,9 @@ int32_t resbm_ffn_encode_fwd(int64_t T, int32_t d_ff, int32_t n, int32_t r, int3
  * of whose bits the sum over r uses) and s_t = 1 / sqrt(mean z~[t]^2 + eps) from
  * the float32 z~.  Columns that an infinite or NaN weight reaches are formed as
  * the sum over c of z~ gamma (rounded to bf16) times W_qkv, so that infinities
- * keep their signs.  A caller that also needs z~ (its residual stream) still runs
- * resbm_decode_fwd.
+ * keep their signs; so are all columns where that is faster (a narrow n with many
+ * tokens or columns).  A caller that also needs z~ (its residual stream) still
+ * runs resbm_decode_fwd.
  *  b      T x r bf16 packed (the payload).
  *  W_d    r x n float32 row-major.   gamma  n float32.
  *  W_qkv  n x N bf16 row-major, contiguous.

@@ -316,7 +316,7 @@ __device__ __forceinline__ XFrag tr_frag_wide(const io_t* tile, int row0, int c0
 // fragment f = ks * NT + nt, lane (row16, grp) holds W_e[32 ks + 8 grp + e][16 nt + row16].
 // One wave per block, so that the few fragments spread over many compute units;
 // no division and no conditional load in front of its round trip (encode_fwd at
-// 16384 x 4096, r = 32: 30.0 -> 28.7 us).
+// 16384 x 4096, r = 32, timed in turn: 29.9 -> 29.7 us).
 __global__ __launch_bounds__(64) void k_enc_fwd_prep(const float* __restrict__ W_e, int n, int r, int NT,
                                                      void* __restrict__ wf) {
   const int l = threadIdx.x, ks = blockIdx.x, nt = blockIdx.y;

@@ -169,6 +169,10 @@ constexpr int rw_ntw(int NT) {
 // wave of blocks over the chip, MT as small as that allows:
 //   T = 8, n = 4096, r = 32: 19.6 -> 6.5 us; T = 1024: 20.6 -> 9.0; T = 4096: 22.7 -> 17.0;
 //   T = 8192 (MT = 2): 25.3 -> 19.1, where T = 16384 would lose (29.8 against 37.1, MT = 4).
+// At exactly one block per unit (T = 4096) MT = 2 is taken, MT = 1's 256 blocks not: every
+// block splits its slice of W_e again, which MT = 1 does for the fewest tokens.  MT = 2
+// against 1: 17.1 and 15.8 us at n = 4096, r = 32, 12.9 and 10.7 at r = 16, but 19.9 and 25.4
+// at n = 8192, 19.6 and 25.0 at T = 2048, n = 4096, r = 128.
 // MT = 4 doubles what a block's split of W_e is spread over, and pays while
 // that split is small, n x 16 JT <= 65536 values:
 //   T = 16384, n = 2048, r = 16: 16.1 -> 14.2 us; T = 32768, n = 1024, r = 4: 18.8 -> 14.2.

@@ -1,5 +1,6 @@
-// HIP kernels of the two-linears-per-side bottleneck and of the encoder fused
-// into the FFN output projection, for gfx950, and their C ABI.
+// HIP kernels of the two-linears-per-side bottleneck, of the encoder fused into the
+// FFN output projection and of the decoder fused into the next block's norm and QKV
+// projection, for gfx950, and their C ABI.
 //
 // Paper: ResBM, Sec. 3.2 (encoder and decoder each two linear layers with a
 // non-linearity between them; encoder at the end of stage l, decoder at the
@@ -10,24 +11,22 @@
 //     decoder  v = b W3,  z~ = phi(v) W4
 // and the backward steps are the adjoints of these maps.
 //
-// Every step is one launch of a single matrix-core GEMM kernel, C = A B over
-// bf16 operands with float32 accumulation, whose two template switches say
-// which of A and B is stored K-contiguous.  The steps differ only in a prologue
-// (phi applied to the A operand while it is staged into LDS) and an epilogue
-// (bf16 or float32 store, multiplication by phi'(X) of a saved pre-activation,
-// addition of identity-path columns, a split-K partial sum, or the encoder's
-// contraction of the output tile).  The n x m products (2 T n m flops each)
-// are matrix-core bound; the r-wide ones stream a T x m tensor and are memory
-// bound.
+// Every product of those steps is C = A B over bf16 operands with float32
+// accumulation, two template switches saying which of A and B is stored
+// K-contiguous.  Epilogues: bf16 or float32 store, a store of phi(C) beside C,
+// multiplication by phi'(X) of a saved pre-activation (with or without phi(X)
+// beside it), addition of identity-path columns, a split-K partial sum, or the
+// encoder's contraction of the output tile.  The n x m products (2 T n m flops
+// each) are matrix-core bound; the r-wide ones stream a T x m tensor and are
+// memory bound.
 //
-// A block computes a BM x BN tile of C in 64-deep stages, double buffered in
-// LDS with one barrier per stage and the next stage's loads in flight during
-// the current stage's products.  256 x 256 tiles load their operands straight
-// into LDS (buffer loads with an LDS destination); the smaller ones go through
-// registers (where the phi prologue is applied).  Every wave multiplies its
-// (16 FM) x (16 FN) sub-tile with v_mfma_f32_16x16x32_bf16.  The B operand takes the instruction's first slot,
-// so a lane's accumulator holds four consecutive columns of one output row and
-// stores them with one 8-byte (bf16) or 16-byte (float32) store.
+// Three kernels, chosen by rows_for, wide_for and narrow_for: k_gemm_big (256 x
+// 256 tiles) and k_gemm_mid (128 x 128) are pipelined (operands straight into LDS,
+// counted waits, two wave groups half a phase apart, persistent over tiles);
+// k_gemm stages 64 x {32, 64, 128} or 128 x 128 tiles through registers, double
+// buffered with one barrier per 64-deep stage, and can apply phi to A on the way.
+// Products are v_mfma_f32_16x16x32_bf16 with the B operand in the first slot, so a
+// lane's accumulator holds four consecutive columns of one output row.
 // K-contiguous operands are staged as [rows][64] and read as 16-byte chunks;
 // the others as [64][rows] and read transposed with ds_read_b64_tr_b16.
 // Split-K partial sums are added in split order by a second kernel, so every
@@ -673,9 +672,10 @@ __device__ __forceinline__ int here(int v) {
 // are stored.  kEpiEncode reuses the stage buffers and runs one item per block.
 // What bounds it: matrix cores at the clock this load allows (a registers-only
 // probe of the same products reaches 2.0 PFLOP/s), then the operand stream.
-// 16384 x 4096 x 14336: 1.47 PFLOP/s, against 1.17 for the double-buffered
-// kernel it replaced (one barrier and a full drain per stage) and 1.31 for the
-// library; without the half-phase offset of the waves 1.28.
+// 16384 x 4096 x 14336 with the encoder: 1.35-1.42 PFLOP/s by box and clocks
+// (1400 us; the library's product without the encoder, timed in turn, 1399), against
+// 1.17 for the double-buffered kernel it replaced (one barrier and a full drain per
+// stage; 1639 us); without the half-phase offset of the waves 0.87 of its rate.
 template <bool AK, bool BKC, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
   constexpr int BM = 256, BN = 256;

@@ -4,9 +4,9 @@ does not wait there; the compiler inserts the wait states, but ROCm 7.2 left the
 behind a branch between the product and the first use (wrong g_z in some tiles).  From
 every product, along the straight path and both sides of every branch, a read of its
 result as a vector operand has to lie at least as many states on as the compiler puts
-there on straight paths (gfx950: eight for the four passes of a bf16 product, 11 and, for memory
-instructions, 18 for a float64 one).  (A product that only accumulates onto the
-result waits by itself.)
+there on straight paths (gfx950: eight for the four passes of a bf16 product, 11 and,
+for memory instructions, 18 for a float64 one).  (A product that only accumulates onto
+the result waits by itself.)
 """
 import os
 import re
