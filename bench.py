@@ -380,7 +380,7 @@ def optimizer_timing(lib, d: dict, r: int, dev, iters: int, cpu: bool) -> dict:
     # short side <= 64: partial Grams of 128-row chunks, the recurrence on the s x s Gram
     # (one block, which adds up to 512 KiB of partials itself; more are one launch
     # more), output pass; wider: load, then per step reduce + poly + row update
-    partials = -(-n // 128) * (-(-r // 4) * 4) ** 2
+    partials = -(-max(d["W_e"].shape) // 128) * (-(-r // 4) * 4) ** 2
     launches = (3 if partials <= 65536 else 4) if r <= 64 else 1 + 3 * steps
     out = {"ns_steps": steps, "coefficients": list(R.NS_QUINTIC),
            "launches_per_update": launches,
