@@ -203,12 +203,14 @@ inline size_t align_ws(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAli
 inline int64_t clamp64(int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // 64-token steps per block of the short backward ops, for `tiles` of them in each of
-// `cols` column groups: as many as leave a block per compute unit, and from four on
-// no block more than there are units (a few more would take a round of their own).
+// `cols` column groups: as many as leave a block per compute unit; from four on no
+// block more than there are units (a few more would take a round of their own),
+// unless that takes half as many steps again.
 inline int64_t once_steps(int64_t tiles, int64_t cols) {
-  int64_t per = clamp64(tiles * cols / kNumCU, 1, tiles);
-  while (per >= 4 && ceil_div(tiles, per) * cols > kNumCU && per < tiles) ++per;
-  return per;
+  const int64_t per = clamp64(tiles * cols / kNumCU, 1, tiles);
+  int64_t one = per;
+  while (ceil_div(tiles, one) * cols > kNumCU && one < tiles) ++one;
+  return per >= 4 && 2 * one < 3 * per ? one : per;
 }
 
 struct Plan {

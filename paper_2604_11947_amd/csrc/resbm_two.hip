@@ -1350,7 +1350,7 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
   __syncthreads();
   constexpr int NI = (WC * KP / 4 + 64 * NW - 1) / (64 * NW);
   float m4[NI][4];
-  int odd = 0;  // an infinity or NaN among this thread's sums
+  int odd = 0;  // an infinity or NaN among this thread's sums (or one that bf16 rounds to infinity)
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int idx = threadIdx.x + i * 64 * NW, c = idx / (KP / 4), j = 4 * (idx % (KP / 4));
@@ -1363,7 +1363,7 @@ __global__ __launch_bounds__(64 * NW) void k_qkv_strip(DqArgs g) {
       }
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) odd |= !isfinite(m4[i][e]);
+    for (int e = 0; e < 4; ++e) odd |= !(fabsf(m4[i][e]) < 3.38e38f);
   }
   if (__syncthreads_or(odd)) {  // (a barrier: the planes overlap the parts)
     qkv_direct<KS, CT, NW>(g, c0, tb, te);
@@ -1799,10 +1799,11 @@ void gemm(Shape s, const GemmArgs& g, int S, hipStream_t st) {
     if (s == kWide) return launch_mid<AK, BKC, EPI>(g, S, st);
     if (s == kFour) return launch<AK, BKC, 128, 128, 2, 2, EPI, false>(g, S, st);
   }
+  if constexpr (EPI == kEpiBf16 || EPI == kEpiAdd || EPI == kEpiF32 || EPI == kEpiPart) {
+    if (s == kNarrow128) return launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st);
+  }
   if (s == kNarrow32) return launch<AK, BKC, 64, 32, 4, 1, EPI, PHI>(g, S, st);
-  if (s == kNarrow64) return launch<AK, BKC, 64, 64, 4, 1, EPI, PHI>(g, S, st);
-  if constexpr (EPI == kEpiBf16 || EPI == kEpiAdd || EPI == kEpiF32 || EPI == kEpiPart)
-    launch<AK, BKC, 64, 128, 4, 1, EPI, PHI>(g, S, st);
+  launch<AK, BKC, 64, 64, 4, 1, EPI, PHI>(g, S, st);
 }
 
 GemmArgs args(int M, int N, int K, const void* A, int64_t lda, size_t ab, const void* B, int64_t ldb, size_t bb,
