@@ -690,19 +690,37 @@ __global__ __launch_bounds__(kDbWaves * 64) void k_dec_bwd(int64_t T, int n, int
   const bool won = wc0 < n;  // n % 64 == 0: a wave's columns lie in [0, n) in whole runs of 64
 
   // W_d as the A operand of g_b: lane (row16, grp) holds W_d[16 (jt0 + jt) + row16][wc0 + 32 ks + 8 grp + e].
+#if !RESBM_IO_F32_BUILD
   const rsrc_t wdr = make_rsrc(W_d, (int64_t)r * n * 4);
+#endif
   SFrag wdf[JT][KSW];
 #pragma unroll
   for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
     for (int ks = 0; ks < KSW; ++ks) {
-      const int j = 16 * (jt0 + jt) + row16, c = wc0 + 32 * ks + 8 * grp;
+      const int j = 16 * (jt0 + jt) + row16;
+#if RESBM_IO_F32_BUILD
+      // (JT = 4 spills 132 registers, and which of them hangs on this form: with buffer loads,
+      // or the column as a 32-bit value first, the step loop is slower, 841 -> 920 us at
+      // 35544 x 3776, r = 52)
+      float w[8];
+      if (wc0 + 32 * ks + 8 * grp < n && j < r) {
+        const float4* p = reinterpret_cast<const float4*>(W_d + (int64_t)j * n + wc0 + 32 * ks + 8 * grp);
+        const float4 a = p[0], c = p[1];
+        w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = c.x; w[5] = c.y; w[6] = c.z; w[7] = c.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = 0.0f;
+      }
+#else
+      const int c = wc0 + 32 * ks + 8 * grp;
       const uint32_t o = c < n && j < r ? (uint32_t)((j * n + c) * 4) : kOOB;
       const uint4 a = bld16(wdr, o), d = bld16(wdr, o == kOOB ? kOOB : o + 16);
       const float w[8] = {__builtin_bit_cast(float, a.x), __builtin_bit_cast(float, a.y),
                           __builtin_bit_cast(float, a.z), __builtin_bit_cast(float, a.w),
                           __builtin_bit_cast(float, d.x), __builtin_bit_cast(float, d.y),
                           __builtin_bit_cast(float, d.z), __builtin_bit_cast(float, d.w)};
+#endif
       wdf[jt][ks] = sfrag_from(w);
     }
 
