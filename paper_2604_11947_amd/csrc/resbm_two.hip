@@ -586,18 +586,27 @@ __device__ __forceinline__ void store_c4(const GemmArgs& g, rsrc_t rc, rsrc_t rx
 // Stores per lane of one store_pair<EPI>.
 constexpr int pair_stores(int epi) { return epi == kEpiF32 || epi == kEpiPart || epi == kEpiBf16Phi || epi == kEpiDphiPhi ? 2 : 1; }
 
+constexpr bool reads_x(int epi) { return epi == kEpiDphi || epi == kEpiDphiPhi || epi == kEpiAdd; }
+// X at the eight columns that this lane stores of a pair (see store_pair).
+template <int EPI>
+__device__ __forceinline__ uint4 load_pair(const GemmArgs& g, rsrc_t rx, int m, int n, int grp) {
+  const int c8 = n - 4 * (grp & 1) + 16 * (grp & 1);  // n = ... + 4 grp
+  const bool ok = m < g.M && c8 < (EPI == kEpiAdd ? g.x_cols : g.N);
+  return bld16(rx, ok ? ((uint32_t)m * (uint32_t)g.ldx + c8) * 2 : kOOB);
+}
+
 // Stores two adjacent 16 x 16 tiles: this lane's four columns n .. n + 3 of the
 // first and n + 16 .. n + 19 of the second, row m.  bf16 results: lanes of even
 // and odd groups exchange halves first, so that each stores eight consecutive
 // columns (even groups of the first tile, odd groups of the second): half the
 // store instructions, 64 bytes of a row each instead of 32 (the two-linear step at
-// 16384 x 4096 x 1024: 872 -> 836 us).
+// 16384 x 4096 x 1024: 872 -> 836 us).  u: what load_pair gave.
 template <int EPI>
-__device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m0,
-                                           int m, int n, int grp, f32x4 v0, f32x4 v1) {
+__device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t rd, int split, int m0, int m, int n,
+                                           int grp, f32x4 v0, f32x4 v1, uint4 u) {
   if constexpr (EPI == kEpiF32 || EPI == kEpiPart) {
-    store_c4<EPI>(g, rc, rx, rd, split, m0, m, n, v0);
-    store_c4<EPI>(g, rc, rx, rd, split, m0, m, n + 16, v1);
+    store_c4<EPI>(g, rc, rc, rd, split, m0, m, n, v0);
+    store_c4<EPI>(g, rc, rc, rd, split, m0, m, n + 16, v1);
   } else {
     f32x4 v[2] = {v0, v1};
     const int c8 = n - 4 * (grp & 1) + 16 * (grp & 1);  // n = ... + 4 grp
@@ -608,9 +617,7 @@ __device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t 
       a = x[0];
       b = x[1];
     };
-    if constexpr (EPI == kEpiDphi || EPI == kEpiDphiPhi || EPI == kEpiAdd) {
-      const bool xok = m < g.M && c8 < (EPI == kEpiAdd ? g.x_cols : g.N);
-      uint4 u = bld16(rx, xok ? ((uint32_t)m * (uint32_t)g.ldx + c8) * 2 : kOOB);
+    if constexpr (reads_x(EPI)) {
       if constexpr (EPI == kEpiDphiPhi)
         bst16(rd, ok ? ((uint32_t)m * (uint32_t)g.ldd + c8) * 2 : kOOB, silu8(u));
       swap(u.x, u.z);
@@ -645,6 +652,44 @@ __device__ __forceinline__ void store_pair(const GemmArgs& g, rsrc_t rc, rsrc_t 
       put(rd, g.ldd, h[0], h[1]);
     }
   }
+}
+
+// Stores a wave's rows mr + row(i), i < FI, and columns nr + 128 q, q < FQ, of a tile at
+// (m0, n0).  X is read for G pairs at a time, ahead of their stores: one load in front
+// of each store left a chain of round trips, each waiting for the stores before it
+// and the stages in flight.  kEpiAdd: only the tiles that hold some of X's columns read it.
+// encode2_bwd with the fused skip gradient, m = 16: 4096 x 4096 50.1 -> 41.1 us, 16384 x
+// 4096 126 -> 99.7 (a block walks tiles of one column there, and one in 32 had the chain);
+// the two-linear step at 16384 x 4096 x 1024: 855 -> 833, timed in turn.
+template <int EPI, int FI, int FQ, int NJ>
+__device__ __forceinline__ void store_rows(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, int split, int m0,
+                                           int mr, int nr, int grp, const f32x4 (&acc)[FI][NJ]) {
+  constexpr int G = 4;  // pairs
+  static_assert(FI * FQ % G == 0 && NJ == 2 * FQ, "groups of pairs cover the tile");
+#pragma unroll
+  for (int p0 = 0; p0 < FI * FQ; p0 += G) {
+    uint4 x[G];
+#pragma unroll
+    for (int p = 0; p < G; ++p) {
+      const int i = (p0 + p) / FQ, q = (p0 + p) % FQ;
+      x[p] = make_uint4(0, 0, 0, 0);
+      if constexpr (reads_x(EPI)) x[p] = load_pair<EPI>(g, rx, mr + (i >> 2) * 128 + (i & 3) * 16, nr + q * 128, grp);
+    }
+#pragma unroll
+    for (int p = 0; p < G; ++p) {
+      const int i = (p0 + p) / FQ, q = (p0 + p) % FQ;
+      store_pair<EPI>(g, rc, rd, split, m0, mr + (i >> 2) * 128 + (i & 3) * 16, nr + q * 128, grp, acc[i][2 * q],
+                      acc[i][2 * q + 1], x[p]);
+    }
+  }
+}
+template <int EPI, int FI, int FQ, int NJ>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, rsrc_t rc, rsrc_t rx, rsrc_t rd, const Item& it, int mr,
+                                           int nr, int grp, const f32x4 (&acc)[FI][NJ]) {
+  if (EPI == kEpiAdd && it.n0 >= g.x_cols)
+    store_rows<EPI == kEpiAdd ? kEpiBf16 : EPI, FI, FQ>(g, rc, rx, rd, it.split, it.m0, mr, nr, grp, acc);
+  else
+    store_rows<EPI, FI, FQ>(g, rc, rx, rd, it.split, it.m0, mr, nr, grp, acc);
 }
 
 // The value v, opaque to the optimizer: what an epilogue derives from it is
@@ -820,12 +865,7 @@ __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
     if constexpr (EPI != kEpiEncode) {
       const rsrc_t rc = out_desc<EPI>(g, cur.m0);
       const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          store_pair<EPI>(g, rc, rx, rd, cur.split, cur.m0, mr + (i >> 2) * 128 + (i & 3) * 16, nr + q * 128, grp,
-                          acc[i][2 * q], acc[i][2 * q + 1]);
+      store_tile<EPI, 8, 2>(g, rc, rx, rd, cur, mr, nr, grp, acc);
     }
     if (EPI == kEpiEncode || !more) break;
     stored = true;
@@ -836,12 +876,7 @@ __global__ __launch_bounds__(512) void k_gemm_big(GemmArgs g, int total) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if constexpr (EPI == kEpiEncode) {
     const rsrc_t rc = out_desc<EPI>(g, cur.m0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-        store_pair<kEpiBf16>(g, rc, rx, rd, 0, 0, cur.m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + row16,
-                             cur.n0 + q * 128 + wn * 32 + 4 * grp, grp, acc[i][2 * q], acc[i][2 * q + 1]);
+    store_rows<kEpiBf16, 8, 2>(g, rc, rx, rd, 0, 0, cur.m0 + wm * 64 + row16, cur.n0 + wn * 32 + 4 * grp, grp, acc);
     encode_epilogue(g, acc, smem, cur.m0, cur.n0);
   }
 }
@@ -931,9 +966,7 @@ __global__ __launch_bounds__(512) void k_gemm_mid(GemmArgs g, int total) {
     }
     const rsrc_t rc = out_desc<EPI>(g, cur.m0);
     const int mr = here(cur.m0 + wm * 64 + row16), nr = here(cur.n0 + wn * 32 + 4 * grp);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      store_pair<EPI>(g, rc, rx, rd, cur.split, cur.m0, mr + 16 * i, nr, grp, acc[i][0], acc[i][1]);
+    store_tile<EPI, 4, 1>(g, rc, rx, rd, cur, mr, nr, grp, acc);
     wl.next += wl.stride;
     if (wl.next >= wl.end) break;
     stored = true;

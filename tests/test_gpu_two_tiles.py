@@ -26,6 +26,8 @@ CASES = [
     (8193, 136, 248, 72),
     (65, 32, 40, 16),         # narrow tiles of 32 and 64 columns
     (130, 64, 24, 8),
+    (4000, 520, 64, 136),     # g_z on 128 x 128 tiles, one column tile with the skip gradient, one with part of it
+    (20000, 520, 136, 264),   # the same on 256 x 256 tiles
 ]
 
 
