@@ -1750,8 +1750,10 @@ Shape narrow_for(int N) { return N <= 32 ? kNarrow32 : (N <= 64 ? kNarrow64 : kN
 //    product), so the small tiles win where they need fewer than twice the rounds, i.e.
 //    where at most 64 large tiles would leave most of the chip idle (1024 x 4096 x
 //    14336: 161 against 258 us; 4096 x 4096 x 14336, 256 large tiles: 582 against 343);
-//    where half a large tile would be padding; and where there is one stage (a pair of stages is the large tiles' step; 35631 x
-//    464 x 32: 22.2 against 25.1).
+//    where half a large tile would be padding; and where there is one stage (a pair of
+//    stages is the large tiles' step; 35631 x 464 x 32: 22.2 against 25.1, but from some
+//    three rounds of large tiles on those are level or better: 28855 x 3384 x 8 51.0
+//    and 51.8, 16384 x 4096 x 32 37.6 and 35.3).
 Shape rows_for(int M, int N, int K) {
   const int64_t big = ((int64_t)(M + 255) / 256) * ((N + 255) / 256), mid = ((int64_t)(M + 127) / 128) * ((N + 127) / 128);
   const int64_t rb = (big + kNumBlocks - 1) / kNumBlocks, rm = (mid + kNumBlocks - 1) / kNumBlocks;
